@@ -108,7 +108,8 @@ typedef struct dpsgd_layer {
  *             widths that are multiples of 64 runs the Gram form, a park
  *             area of at most 128 MB (256 KB per workgroup of that kernel,
  *             or, when few tiles are split along the columns, two 256 KB
- *             partial tiles per part).
+ *             partial tiles per part), or, when the Gram-form layers have few
+ *             tiles in all, at most 112 partial tiles of 64 KB.
  * T = 1 layers always use the closed form ||a||^2 ||g||^2 whatever the mode.
  * ------------------------------------------------------------------------- */
 size_t dpsgd_norms_workspace_bytes(const dpsgd_layer* layers, int32_t n_layers, int32_t mode);

@@ -50,7 +50,7 @@ int check_layers(const dpsgd_layer* layers, int32_t n, bool data) {
 }
 
 // Norm workspace: partials [B][P], then (when a layer runs the Gram form on
-// 256-row tiles) the park area of those tiles.
+// 256-row tiles or with its columns split) the park area of those tiles.
 struct NormPlan {
   std::vector<NormForm> forms;
   std::vector<int64_t> cols;
@@ -66,6 +66,25 @@ struct NormPlan {
 // 256-row tiles where the layer qualifies and a park area is allowed.
 NormForm planned_form(const dpsgd_layer& L, NormForm f, bool park_ok) {
   return f == FORM_GHOST && park_ok && ghost256_ok(L) ? FORM_GHOST256 : f;
+}
+
+// Moves the Gram-form layers of a call with few tiles to the split form, when
+// partials and partial tiles together fit the allocation-free call's scratch
+// (so that it runs the same kernels). Layers that the workspace call runs on
+// 256-row tiles do not take part.
+void split_few_tiles(const dpsgd_layer* layers, int32_t n, NormPlan* p) {
+  std::vector<int> idx;
+  int64_t cols = 0;
+  for (int32_t l = 0; l < n; ++l) {
+    if (p->forms[l] == FORM_GHOST && !gram64_ok(layers[l]) && !ghost256_ok(layers[l])) idx.push_back(l);
+  }
+  if (!ghost_split_wanted(layers, idx.data(), (int)idx.size())) return;
+  std::vector<NormForm> forms = p->forms;
+  for (int l : idx) forms[l] = FORM_GHOST_SPLIT;
+  for (int32_t l = 0; l < n; ++l) cols += norm_partials_per_example(layers[l], forms[l]);
+  const size_t bytes = round_up((size_t)layers[0].B * (size_t)cols * sizeof(float), 256) +
+                       ghost_split_park_bytes(layers, idx.data(), (int)idx.size());
+  if (bytes <= DPSGD_NOALLOC_SCRATCH_BYTES) p->forms.swap(forms);
 }
 
 // Fills cols, P, park_off and bytes from forms. The park area is the largest
@@ -85,6 +104,10 @@ void finish_norm_plan(const dpsgd_layer* layers, int32_t n, NormPlan* p) {
       if (p->forms[l] == FORM_GHOST256) idx.push_back(l);
     if (!idx.empty()) park = std::max(park, ghost256_park_bytes(layers, idx.data(), (int)idx.size()));
   }
+  idx.clear();
+  for (int32_t l = 0; l < n; ++l)
+    if (p->forms[l] == FORM_GHOST_SPLIT) idx.push_back(l);
+  park = std::max(park, ghost_split_park_bytes(layers, idx.data(), (int)idx.size()));
   p->park_off = round_up((size_t)layers[0].B * (size_t)p->P * sizeof(float), 256);
   p->bytes = p->park_off + park;
 }
@@ -95,6 +118,7 @@ NormPlan plan_norms(const dpsgd_layer* layers, int32_t n, int32_t mode, bool par
   p.cols.resize(n);
   for (int32_t l = 0; l < n; ++l)
     p.forms[l] = planned_form(layers[l], resolve_norm_form(layers[l], mode), park_ok);
+  split_few_tiles(layers, n, &p);
   finish_norm_plan(layers, n, &p);
   return p;
 }
@@ -146,6 +170,7 @@ StepPlan plan_step(const dpsgd_layer* layers, int32_t n, int32_t mode) {
         stored ? FORM_STORED : planned_form(layers[l], resolve_norm_form(layers[l], mode), true);
     (stored ? p.stored : p.other).push_back(l);
   }
+  split_few_tiles(layers, n, &p.norms);
   finish_norm_plan(layers, n, &p.norms);
   const int64_t B = layers[0].B;
   for (int l : p.other) p.other_layers.push_back(layers[l]);
@@ -255,7 +280,8 @@ int dpsgd_per_example_norms_multi_noalloc(const dpsgd_layer* layers, int32_t n_l
   if (st != DPSGD_OK) return st;
   if (!valid_mode(mode)) return DPSGD_ERR_UNSUPPORTED;
   if (!norms_sq) return DPSGD_ERR_INVALID_ARG;
-  // No park area: T > 256 Gram-form layers take the 128-row tiles here.
+  // No 256-row tiles, whose park area the scratch does not hold: T > 256
+  // Gram-form layers take the 128-row tiles here.
   const NormPlan p = plan_norms(layers, n_layers, mode, false);
   if (p.bytes > DPSGD_NOALLOC_SCRATCH_BYTES) return DPSGD_ERR_WORKSPACE;
   void* ws = scratch_on_current_device(&st);
@@ -263,7 +289,7 @@ int dpsgd_per_example_norms_multi_noalloc(const dpsgd_layer* layers, int32_t n_l
   // Every partial slot [i][col] of the plan is written by exactly one job
   // before the reduction reads it, so the scratch needs no clearing.
   return launch_norms(layers, p.forms.data(), n_layers, norms_sq, accumulate ? 1 : 0,
-                      static_cast<float*>(ws), p.P, p.cols.data(), nullptr,
+                      static_cast<float*>(ws), p.P, p.cols.data(), p.park(ws),
                       static_cast<hipStream_t>(stream));
 }
 

@@ -18,7 +18,17 @@ constexpr int kMaxLayersPerLaunch = 48;  // entries of a per-launch layer table 
 // layer with a narrow side are formed once, stored and normed (skinny.hip).
 // FORM_GHOST256: the Gram form on 256-row tiles (T > 256, ghost.hip), chosen
 // by the workspace plans for FORM_GHOST layers that qualify.
-enum NormForm : int { FORM_T1 = 0, FORM_GHOST = 1, FORM_MAT = 2, FORM_STORED = 3, FORM_GHOST256 = 4 };
+// FORM_GHOST_SPLIT: the Gram form with every tile's columns split over several
+// workgroups (norms.hip), chosen by the workspace plans when a call has few
+// tiles.
+enum NormForm : int {
+  FORM_T1 = 0,
+  FORM_GHOST = 1,
+  FORM_MAT = 2,
+  FORM_STORED = 3,
+  FORM_GHOST256 = 4,
+  FORM_GHOST_SPLIT = 5
+};
 constexpr int64_t kSkinnyMaxRank = 16;   // narrow side of a FORM_STORED layer
 
 // ----------------------------------------------------------- device helpers
@@ -128,6 +138,12 @@ int64_t ghost256_cols(const dpsgd_layer& L);
 size_t ghost256_park_bytes(const dpsgd_layer* layers, const int* idx, int n);
 int launch_ghost256(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
                     float* partials, int64_t P, float* park, hipStream_t stream);
+
+// Gram form with the columns split (norms.hip): whether a call whose Gram-form
+// layers (T <= 256, or no 256-row tiles) are idx[0..n) has few enough tiles,
+// and the partial Gram tiles' bytes.
+bool ghost_split_wanted(const dpsgd_layer* layers, const int* idx, int n);
+size_t ghost_split_park_bytes(const dpsgd_layer* layers, const int* idx, int n);
 
 bool tr_tile_ok(const dpsgd_layer& L);
 // k-major float32 kernel (gemm.hip): float32, T a multiple of 32, d_in and d_out

@@ -16,6 +16,8 @@
 // multiplied element-wise and summed. Each tile writes one float partial;
 // a final fixed-order reduction adds the partials of every layer of the call
 // into norms_sq, so the result does not depend on scheduling.
+#include <vector>
+
 #include "mma.h"
 
 namespace dpsgd {
@@ -81,6 +83,10 @@ __device__ __forceinline__ uint4 load_chunk(const TIn* X, int64_t ld, int row, i
   const TIn* p = X + (int64_t)row * ld + k;
   if (VEC) {
     if (k < d) v = *reinterpret_cast<const uint4*>(p);
+  } else if (k + E <= d) {
+    // Rows of other widths start at any element: one 16-byte load without an
+    // alignment (global loads need none here) instead of eight or four.
+    __builtin_memcpy(&v, p, 16);
   } else {
     uint32_t w[4] = {0u, 0u, 0u, 0u};
     if (E == 8) {
@@ -121,10 +127,12 @@ __device__ __forceinline__ void store_tile_rows(TIn* Xs, const uint4 (&r)[4]) {
   }
 }
 
-// acc = Xp[rows_p] Xq[rows_q]^T over k in [0, d), double-buffered through LDS.
+// acc = Xp[rows_p] Xq[rows_q]^T over k in [0, d) of rows of length ld,
+// double-buffered through LDS.
 template <typename TIn, bool VEC>
-__device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int d, int rows_p,
-                                           int rows_q, bool diag, f32x4_t (&acc)[4][4],
+__device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int64_t ld, int d,
+                                           int rows_p, int rows_q, bool diag,
+                                           f32x4_t (&acc)[4][4],
                                            TIn* lds /* [2 stages][2 operands][OPE] */) {
   constexpr int BK = TileCfg<TIn>::BK;
   constexpr int SK = TileCfg<TIn>::SK;
@@ -135,8 +143,8 @@ __device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int d, 
   const int nsteps = (d + BK - 1) / BK;
   uint4 rp[4], rq[4];
   zero_acc(acc);
-  load_tile_rows<TIn, VEC>(Xp, d, rows_p, 0, d, rp);
-  if (!diag) load_tile_rows<TIn, VEC>(Xq, d, rows_q, 0, d, rq);
+  load_tile_rows<TIn, VEC>(Xp, ld, rows_p, 0, d, rp);
+  if (!diag) load_tile_rows<TIn, VEC>(Xq, ld, rows_q, 0, d, rq);
   store_tile_rows<TIn>(lds, rp);
   if (!diag) store_tile_rows<TIn>(lds + OPE, rq);
   __syncthreads();
@@ -144,8 +152,8 @@ __device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int d, 
     const int cur = s & 1;
     const bool more = s + 1 < nsteps;
     if (more) {
-      load_tile_rows<TIn, VEC>(Xp, d, rows_p, (s + 1) * BK, d, rp);
-      if (!diag) load_tile_rows<TIn, VEC>(Xq, d, rows_q, (s + 1) * BK, d, rq);
+      load_tile_rows<TIn, VEC>(Xp, ld, rows_p, (s + 1) * BK, d, rp);
+      if (!diag) load_tile_rows<TIn, VEC>(Xq, ld, rows_q, (s + 1) * BK, d, rq);
     }
     const TIn* P = lds + cur * 2 * OPE;
     const TIn* Q = diag ? P : P + OPE;
@@ -190,9 +198,9 @@ __global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
 
   f32x4_t accA[4][4], accG[4][4];
   gram_phase<TIn, VEC>(A + (int64_t)p * kTile * E.d_in, A + (int64_t)q * kTile * E.d_in, E.d_in,
-                       rows_p, rows_q, diag, accA, lds);
+                       E.d_in, rows_p, rows_q, diag, accA, lds);
   gram_phase<TIn, VEC>(G + (int64_t)p * kTile * E.d_out, G + (int64_t)q * kTile * E.d_out, E.d_out,
-                       rows_p, rows_q, diag, accG, lds);
+                       E.d_out, rows_p, rows_q, diag, accG, lds);
   float s = 0.f;
 #pragma unroll
   for (int a = 0; a < 4; ++a)
@@ -202,6 +210,109 @@ __global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
       for (int v = 0; v < 4; ++v) s = fmaf(accA[a][b][v], accG[a][b][v], s);
   s = block_sum(s, red);
   if (threadIdx.x == 0) args.partials[i * args.P + E.partial_col + pr] = diag ? s : 2.0f * s;
+}
+
+// ------------------------------------------- ghost, tiles split by columns
+//
+// A call with few examples and short sequences has fewer tiles than the GPU
+// has CUs, and each tile would walk all d_in + d_out columns alone. Here the
+// column slices of every tile are dealt to `parts` workgroups (parts_a of them
+// take A's slices, the rest G's). Each writes its float32 partial Gram tile to
+// the workspace, in register order (64 KB, 16 bytes a lane), and a second
+// kernel adds a tile's parts in order, multiplies GA by GG and sums. 768 ->
+// 50257 in bf16 with B = 4, T = 128: 4.6 ms with one workgroup a tile (four in
+// all); with the split, norms and clipped sum together went from 6.91 to 0.50
+// ms. At most kGsMaxJobs parts run, so that the partial tiles fit the
+// allocation-free call's scratch and both calls run the same kernels.
+
+constexpr int kGsTileFloats = kTile * kTile;   // one partial Gram tile
+constexpr int64_t kGsMaxJobs = 112;            // partial tiles of a call (7 MB)
+constexpr int kGsChunks = 16;                  // combine workgroups (and norm partials) per tile
+
+
+struct GsEntry {
+  const void* A;
+  const void* G;
+  int32_t d_in, d_out, T;
+  int32_t nt, pairs;
+  int32_t parts_a, parts;
+  uint32_t wg_begin;      // first part job of this layer in the launch
+  uint32_t tile_begin;    // first tile of this layer in the launch
+  int32_t partial_col;
+};
+struct GsArgs {
+  GsEntry L[kMaxLayersPerLaunch];
+  int32_t n;
+  int64_t P;
+  float* partials;
+  float* park;            // [jobs][kGsTileFloats]
+};
+
+// Row blocks (p, q), p <= q, of tile pr of the row-major upper triangle.
+__device__ __forceinline__ void tile_pair(int nt, int pr, int* p, int* q) {
+  int pp = 0, rem = pr;
+  while (rem >= nt - pp) { rem -= nt - pp; ++pp; }
+  *p = pp;
+  *q = pp + rem;
+}
+
+template <typename TIn, bool VEC>
+__global__ __launch_bounds__(kThreads, 2) void ghost_part_kernel(GsArgs args) {
+  constexpr int OPE = lds_operand_elems<TIn>();
+  constexpr int BK = TileCfg<TIn>::BK;
+  __shared__ __attribute__((aligned(16))) TIn lds[2 * 2 * OPE];
+  int l = 0;
+  while (l + 1 < args.n && args.L[l + 1].wg_begin <= blockIdx.x) ++l;
+  const GsEntry& E = args.L[l];
+  const uint32_t w = blockIdx.x - E.wg_begin;
+  const int part = (int)(w % (uint32_t)E.parts);
+  const uint32_t tile = w / (uint32_t)E.parts;
+  const int64_t i = tile / (uint32_t)E.pairs;
+  int p, q;
+  tile_pair(E.nt, (int)(tile % (uint32_t)E.pairs), &p, &q);
+  const bool is_a = part < E.parts_a;
+  const int d = is_a ? E.d_in : E.d_out;
+  const int np = is_a ? E.parts_a : E.parts - E.parts_a, pi = is_a ? part : part - E.parts_a;
+  const int slices = (d + BK - 1) / BK;
+  const int k0 = (int)((int64_t)slices * pi / np) * BK;
+  const int k1 = min((int)((int64_t)slices * (pi + 1) / np) * BK, d);
+  const TIn* X = static_cast<const TIn*>(is_a ? E.A : E.G) + i * (int64_t)E.T * d + k0;
+  f32x4_t acc[4][4];
+  gram_phase<TIn, VEC>(X + (int64_t)p * kTile * d, X + (int64_t)q * kTile * d, d, k1 - k0,
+                       min(kTile, E.T - p * kTile), min(kTile, E.T - q * kTile), p == q, acc, lds);
+  float* dst = args.park + (int64_t)blockIdx.x * kGsTileFloats + 4 * threadIdx.x;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      *reinterpret_cast<f32x4_t*>(dst + (4 * a + b) * 4 * kThreads) = acc[a][b];
+}
+
+// One workgroup per tile and 1/16 of its elements (one float4 a thread).
+__global__ __launch_bounds__(kThreads) void ghost_part_combine_kernel(GsArgs args) {
+  __shared__ float red[4];
+  const uint32_t tile_g = blockIdx.x / kGsChunks;
+  const int chunk = (int)(blockIdx.x % kGsChunks);
+  int l = 0;
+  while (l + 1 < args.n && args.L[l + 1].tile_begin <= tile_g) ++l;
+  const GsEntry& E = args.L[l];
+  const uint32_t tile = tile_g - E.tile_begin;
+  const int64_t i = tile / (uint32_t)E.pairs;
+  const int pr = (int)(tile % (uint32_t)E.pairs);
+  const float* src = args.park + ((int64_t)E.wg_begin + (int64_t)tile * E.parts) * kGsTileFloats +
+                     chunk * 4 * kThreads + 4 * threadIdx.x;
+  f32x4_t ga = {0.f, 0.f, 0.f, 0.f}, gg = {0.f, 0.f, 0.f, 0.f};
+  const int na = E.parts_a, n = E.parts;
+#pragma unroll 8
+  for (int s = 0; s < na; ++s) ga += *reinterpret_cast<const f32x4_t*>(src + (int64_t)s * kGsTileFloats);
+#pragma unroll 8
+  for (int s = na; s < n; ++s) gg += *reinterpret_cast<const f32x4_t*>(src + (int64_t)s * kGsTileFloats);
+  float v = fmaf(ga[0], gg[0], fmaf(ga[1], gg[1], fmaf(ga[2], gg[2], ga[3] * gg[3])));
+  v = block_sum(v, red);
+  int p, q;
+  tile_pair(E.nt, pr, &p, &q);
+  if (threadIdx.x == 0)
+    args.partials[i * args.P + E.partial_col + pr * kGsChunks + chunk] = p == q ? v : 2.0f * v;
 }
 
 // ---------------------------------------------------------- reduce, factors
@@ -297,6 +408,78 @@ bool ghost_vec_ok(const dpsgd_layer& L) {
   return L.d_in % E == 0 && L.d_out % E == 0;
 }
 
+// Parts of a split layer's A and G columns when a part takes `chunk` slices.
+struct GsParts {
+  int64_t a, g;
+};
+GsParts gs_parts(const dpsgd_layer& L, int64_t chunk) {
+  const int64_t bk = L.dtype == DPSGD_BF16 ? TileCfg<uint16_t>::BK : TileCfg<float>::BK;
+  return {ceil_div(ceil_div(L.d_in, bk), chunk), ceil_div(ceil_div(L.d_out, bk), chunk)};
+}
+int64_t gs_tiles(const dpsgd_layer& L) {
+  const int64_t nt = ceil_div(L.T, kTile);
+  return L.B * (nt * (nt + 1) / 2);
+}
+int64_t gs_jobs(const dpsgd_layer* layers, const int* idx, int n, int64_t chunk) {
+  int64_t jobs = 0;
+  for (int k = 0; k < n; ++k) {
+    const GsParts s = gs_parts(layers[idx[k]], chunk);
+    jobs += gs_tiles(layers[idx[k]]) * (s.a + s.g);
+  }
+  return jobs;
+}
+// Slices per part: the fewest (at least four) whose parts fit kGsMaxJobs.
+int64_t gs_chunk(const dpsgd_layer* layers, const int* idx, int n) {
+  int64_t lo = 4, hi = 4;
+  while (gs_jobs(layers, idx, n, hi) > kGsMaxJobs && hi < (INT64_C(1) << 32)) hi *= 2;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (gs_jobs(layers, idx, n, mid) <= kGsMaxJobs) hi = mid; else lo = mid + 1;
+  }
+  return lo;
+}
+
+template <typename TIn, bool VEC>
+int launch_ghost_split(const dpsgd_layer* layers, const int* idx, int n, int64_t chunk,
+                       const int64_t* cols, float* partials, int64_t P, float* park,
+                       hipStream_t stream) {
+  for (int base = 0; base < n; base += kMaxLayersPerLaunch) {
+    const int m = n - base < kMaxLayersPerLaunch ? n - base : kMaxLayersPerLaunch;
+    GsArgs args{};
+    args.n = m;
+    args.P = P;
+    args.partials = partials;
+    args.park = park;
+    int64_t jobs = 0, tiles = 0;
+    for (int k = 0; k < m; ++k) {
+      const dpsgd_layer& L = layers[idx[base + k]];
+      const GsParts s = gs_parts(L, chunk);
+      GsEntry& E = args.L[k];
+      E.A = L.A;
+      E.G = L.G;
+      E.d_in = (int32_t)L.d_in;
+      E.d_out = (int32_t)L.d_out;
+      E.T = (int32_t)L.T;
+      E.nt = (int32_t)ceil_div(L.T, kTile);
+      E.pairs = E.nt * (E.nt + 1) / 2;
+      E.parts_a = (int32_t)s.a;
+      E.parts = (int32_t)(s.a + s.g);
+      E.wg_begin = (uint32_t)jobs;
+      E.tile_begin = (uint32_t)tiles;
+      E.partial_col = (int32_t)cols[idx[base + k]];
+      jobs += gs_tiles(L) * E.parts;
+      tiles += gs_tiles(L);
+    }
+    hipLaunchKernelGGL((ghost_part_kernel<TIn, VEC>), dim3((uint32_t)jobs), dim3(kThreads), 0,
+                       stream, args);
+    if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
+    hipLaunchKernelGGL(ghost_part_combine_kernel, dim3((uint32_t)(tiles * kGsChunks)),
+                       dim3(kThreads), 0, stream, args);
+    if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
+  }
+  return DPSGD_OK;
+}
+
 template <typename TIn>
 int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_layers,
                        float* partials, int64_t P, const int64_t* cols, float* park,
@@ -309,8 +492,15 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
   int idx_g4[256], n_g4 = 0;
   int idx_g64[256], n_g64 = 0;
   int idx_mat[256], n_mat = 0;
+  int idx_sv[256], n_sv = 0;
+  int idx_ss[256], n_ss = 0;
+  // The part size is planned over all split layers of the call.
+  std::vector<int> split;
+  for (int l = 0; l < n_layers; ++l)
+    if (forms[l] == FORM_GHOST_SPLIT) split.push_back(l);
+  const int64_t chunk = split.empty() ? 0 : gs_chunk(layers, split.data(), (int)split.size());
   for (int base = 0; base < n_layers; base += 256) {
-    n_t1 = n_gv = n_gs = n_gd = n_g4 = n_g64 = n_mat = 0;
+    n_t1 = n_gv = n_gs = n_gd = n_g4 = n_g64 = n_mat = n_sv = n_ss = 0;
     const int m = n_layers - base < 256 ? n_layers - base : 256;
     for (int k = 0; k < m; ++k) {
       const int l = base + k;
@@ -318,6 +508,10 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
         case FORM_T1: idx_t1[n_t1++] = l; break;
         case FORM_STORED: break;   // skinny.hip
         case FORM_GHOST256: idx_g4[n_g4++] = l; break;
+        case FORM_GHOST_SPLIT:
+          if (ghost_vec_ok<TIn>(layers[l])) idx_sv[n_sv++] = l;
+          else idx_ss[n_ss++] = l;
+          break;
         case FORM_GHOST:
           if (ghost_dma_ok(layers[l])) idx_gd[n_gd++] = l;
           else if (gram64_ok(layers[l])) idx_g64[n_g64++] = l;
@@ -333,6 +527,10 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
       st = launch_ghost_group<TIn, true>(layers, idx_gv, n_gv, cols, partials, P, stream);
     if (st == DPSGD_OK && n_gs)
       st = launch_ghost_group<TIn, false>(layers, idx_gs, n_gs, cols, partials, P, stream);
+    if (st == DPSGD_OK && n_sv)
+      st = launch_ghost_split<TIn, true>(layers, idx_sv, n_sv, chunk, cols, partials, P, park, stream);
+    if (st == DPSGD_OK && n_ss)
+      st = launch_ghost_split<TIn, false>(layers, idx_ss, n_ss, chunk, cols, partials, P, park, stream);
     if (st == DPSGD_OK && n_gd) st = launch_ghost_dma(layers, idx_gd, n_gd, cols, partials, P, stream);
     if (st == DPSGD_OK && n_g4)
       st = launch_ghost256(layers, idx_g4, n_g4, cols, partials, P, park, stream);
@@ -345,6 +543,25 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
 }
 
 }  // namespace
+
+bool ghost_split_wanted(const dpsgd_layer* layers, const int* idx, int n) {
+  // At most a third as many tiles as parts, and a part at most a third of the
+  // longest walk over a tile's columns: then the extra pass over the partial
+  // tiles is paid back. (Every tile takes a part for A and one for G.)
+  int64_t tiles = 0, longest = 0;
+  for (int k = 0; k < n; ++k) {
+    const GsParts s = gs_parts(layers[idx[k]], 1);
+    tiles += gs_tiles(layers[idx[k]]);
+    if (s.a + s.g > longest) longest = s.a + s.g;
+  }
+  if (n <= 0 || 3 * tiles > kGsMaxJobs) return false;
+  return longest >= 3 * gs_chunk(layers, idx, n);
+}
+
+size_t ghost_split_park_bytes(const dpsgd_layer* layers, const int* idx, int n) {
+  if (n <= 0) return 0;
+  return (size_t)gs_jobs(layers, idx, n, gs_chunk(layers, idx, n)) * kGsTileFloats * sizeof(float);
+}
 
 NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode) {
   if (L.T == 1) return FORM_T1;
@@ -369,6 +586,10 @@ int64_t norm_partials_per_example(const dpsgd_layer& L, NormForm form) {
     case FORM_T1: return 1;
     case FORM_STORED: return skinny_chunks(L);
     case FORM_GHOST256: return ghost256_cols(L);
+    case FORM_GHOST_SPLIT: {
+      const int64_t nt = ceil_div(L.T, kTile);
+      return kGsChunks * (nt * (nt + 1) / 2);
+    }
     case FORM_GHOST: {
       const int64_t nt = ceil_div(L.T, kTile);
       return nt * (nt + 1) / 2;
