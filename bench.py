@@ -39,7 +39,7 @@ METRIC = "DP-SGD clipped+noised grad throughput: examples/s per layer; % MFMA pe
 # record per workload; valid only for the kernel sources they were taken with.
 TRAFFIC_FILE = os.path.join(HERE, "profiles", "clip_gemm_{workload}_traffic.txt")
 GEMM_SOURCES = [os.path.join(HERE, "paper_2609_20532_amd", "csrc", f)
-                for f in ("gemm_wide.hip", "gemm_tr.hip", "gemm.hip", "lds_dma.h", "mma.h",
+                for f in ("gemm_wide.hip", "gemm_tr.hip", "gemm_any.hip", "gemm.hip", "lds_dma.h", "mma.h",
                           "common.h")]
 
 
@@ -48,10 +48,10 @@ def dominant_kernel(W) -> str:
     rules): bf16 on the 384x256-tile kernel when d_in % 256 == 0, T % 64 == 0 and
     d_out % 384 == 0, or d_out % 32 == 0 with a ragged last row tile padding at
     most 6 % on a layer of at least one tile per CU; else bf16 on the 256x256-tile
-    kernel when both widths are multiples of 256; else the 128-tile kernel."""
+    kernel when both widths are multiples of 256; else the any-shape kernel."""
     s = max(W.layers, key=lambda s: s.d_in * s.d_out)
     if W.dtype != "bf16":
-        return "tgemm_kernel"
+        return "tgemm_any_kernel"
     tiles_m = -(-s.d_out // 384)
     pad = tiles_m * 384 - s.d_out
     ragged = s.d_out % 32 == 0 and 50 * pad <= 3 * s.d_out and tiles_m * (s.d_in // 256) >= 256
@@ -59,7 +59,7 @@ def dominant_kernel(W) -> str:
         return "tgemm_wide_kernel"
     if s.d_in % 256 == 0 and s.d_out % 256 == 0 and W.T % 32 == 0:
         return "tgemm_tr_kernel<0>"
-    return "tgemm_kernel"
+    return "tgemm_any_kernel"
 
 
 def parse():

@@ -40,11 +40,12 @@ __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w 
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// Round two floats to bf16 (nearest-even) and pack them (lo in bits 0..15).
+// Round two floats to bf16 (nearest-even) and pack them (lo in bits 0..15):
+// one v_cvt_pk_bf16_f32.
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  __bf16 a = (__bf16)lo;
-  __bf16 b = (__bf16)hi;
-  return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{lo, hi}), bf16x2_t));
 }
 
 // Deterministic sum over a wave64 (fixed butterfly order).
@@ -146,17 +147,32 @@ bool ghost_split_wanted(const dpsgd_layer* layers, const int* idx, int n);
 size_t ghost_split_park_bytes(const dpsgd_layer* layers, const int* idx, int n);
 
 bool tr_tile_ok(const dpsgd_layer& L);
-// k-major float32 kernel (gemm.hip): float32, T a multiple of 32, d_in and d_out
-// multiples of 4 and at most 2^24. Tiles are 64 x 256 for d_out <= 64, else
-// 128 x 128 (rows along d_out, columns along d_in).
-bool k32_ok(const dpsgd_layer& L);
-int k32_tile_m(const dpsgd_layer& L);
-int k32_tile_n(const dpsgd_layer& L);
-int k32_ex_per_job(const dpsgd_layer& L);   // examples per materialised-norm job
-// Layers whose g_i has at most 512 entries (gemm.hip) form g_i on the VALU:
-// one norm partial per example; the clip runs tiny_jobs(L) jobs of
-// consecutive examples, one partial sum each.
-bool tiny_ok(const dpsgd_layer& L);
+// Any-shape kernel (gemm_any.hip): every float32 layer and the bf16 layers that
+// the larger tiles and the VALU kernel do not take. Tiles (any_shape) are 64 x
+// 192 for d_out <= 64, else 128 x 128 (rows along d_out, columns along d_in).
+// any_flat: the clip weight goes to the operand (always in float32), otherwise
+// to the accumulator. any_slices: K slices (of any_slice_rows rows) of a clip.
+bool any_flat(const dpsgd_layer& L);
+int any_shape(const dpsgd_layer& L);
+int64_t any_tiles_n(const dpsgd_layer& L);
+int64_t any_tiles(const dpsgd_layer& L);
+int any_slice_rows(const dpsgd_layer& L);
+int64_t any_slices(const dpsgd_layer& L);
+double any_tile_area(const dpsgd_layer& L);
+int any_workgroups_per_cu();
+bool any_slow(const dpsgd_layer& L);   // widths below 16 bytes and others: a kernel of its own
+int any_ex_per_job(const dpsgd_layer& L);   // examples per materialised-norm job
+// The layers of one launch have one dtype, shape, any_slow and (clip) weight mode.
+int launch_any_clip(const dpsgd_layer* layers, const int* idx, int n, const float* factors,
+                    float* const* outs, const int* splits, const int* accumulate,
+                    hipStream_t stream);
+int launch_any_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
+                     float* partials, int64_t P, hipStream_t stream);
+// Layers whose g_i has at most 512 entries may form g_i on the VALU (gemm.hip):
+// one norm partial per example; the clip runs tiny_jobs(L) jobs of consecutive
+// examples, one partial sum each.
+bool tiny_clip_ok(const dpsgd_layer& L);
+bool tiny_norm_ok(const dpsgd_layer& L);
 int tiny_jobs(const dpsgd_layer& L);
 // Output tiles of the materialised-norm kernel that takes the layer (one norm
 // partial per tile and example).

@@ -1,7 +1,7 @@
-// MFMA tile machinery shared by the Gram (ghost-norm) and the transposed-operand
-// GEMM kernels (clip-weighted sum, materialised norm).
+// MFMA tile machinery of the general Gram (ghost-norm) kernel, and the job
+// orders and element loads that several kernels share.
 //
-// A workgroup computes a 128x128 fp32 tile with 4 wave64s in a 2x2 grid; each
+// A Gram workgroup computes a 128x128 fp32 tile with 4 wave64s in a 2x2 grid; each
 // wave owns a 64x64 sub-tile as 4x4 blocks of the 16x16 MFMA output.
 //
 // Both operands of a K step sit in LDS as [row][k] with k contiguous (row
@@ -41,13 +41,6 @@ __device__ __forceinline__ void zero_acc(f32x4_t (&acc)[4][4]) {
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-}
-
-__device__ __forceinline__ void scale_acc(f32x4_t (&acc)[4][4], float s) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] *= s;
 }
 
 // acc += As[64 rows] . Bs[64 rows]^T over one K step held in LDS.
@@ -107,56 +100,6 @@ __device__ __forceinline__ void mma_step(const float* __restrict__ As, const flo
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][h].w, b[j][h].w, acc[i][j], 0, 0, 0);
         }
     }
-  }
-}
-
-// Generic bf16 wave tile: acc[MB][NB] += As[MB*16 rows] . Bs[NB*16 rows]^T over one
-// K step of BK = 64 in LDS (same operand and output layout as mma_step above).
-// With RESCALE, every accumulator block is multiplied by `s` just before its
-// first MFMA of the step, so only a few blocks are in flight in VGPRs at a time.
-template <int MB, int NB, bool RESCALE = false>
-__device__ __forceinline__ void mma_tile_bf16(const uint16_t* __restrict__ As,
-                                              const uint16_t* __restrict__ Bs,
-                                              f32x4_t (&acc)[MB][NB], int lane, float s = 1.0f) {
-  constexpr int SK = TileCfg<uint16_t>::SK;
-  const int r = lane & 15;
-  const int ko = (lane >> 4) * 8;
-#pragma unroll
-  for (int kc = 0; kc < TileCfg<uint16_t>::BK / 32; ++kc) {
-    bf16x8_t b[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      b[j] = *reinterpret_cast<const bf16x8_t*>(Bs + (j * 16 + r) * SK + kc * 32 + ko);
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(As + (i * 16 + r) * SK + kc * 32 + ko);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const f32x4_t c = (RESCALE && kc == 0) ? acc[i][j] * s : acc[i][j];
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[j], c, 0, 0, 0);
-      }
-    }
-  }
-}
-
-template <int MB, int NB>
-__device__ __forceinline__ void zero_acc_t(f32x4_t (&acc)[MB][NB]) {
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-}
-
-// Multiplies the accumulators by s one block row at a time; the scheduling
-// barriers keep the compiler from reading every accumulator register into
-// VGPRs at once (the accumulators of large wave tiles live in AGPRs).
-template <int MB, int NB>
-__device__ __forceinline__ void scale_acc_t(f32x4_t (&acc)[MB][NB], float s) {
-#pragma unroll
-  for (int i = 0; i < MB; ++i) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] *= s;
-    __builtin_amdgcn_sched_barrier(0);
   }
 }
 

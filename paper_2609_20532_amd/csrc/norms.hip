@@ -575,9 +575,8 @@ NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode) {
   const double ghost = gram64_ok(L) ? (double)(L.d_in + L.d_out) / 4.0
                                     : (double)(nt * (nt + 1) / 2) *
                                           (double)(ceil_div(L.d_in, bk) * bk + ceil_div(L.d_out, bk) * bk);
-  // (A k-major float32 tile, 64 x 256 or 128 x 128, has the area of a 128 x 128 one.)
-  const int64_t mt = k32_ok(L) ? mat_tile_count(L) : ceil_div(L.d_out, kTile) * ceil_div(L.d_in, kTile);
-  const double mat = (double)mt * (double)(ceil_div(L.T, bk) * bk);
+  const double mt = (double)any_tiles(L) * any_tile_area(L) / (kTile * kTile);
+  const double mat = mt * (double)(ceil_div(L.T, bk) * bk);
   return ghost <= mat ? FORM_GHOST : FORM_MAT;
 }
 
@@ -594,8 +593,7 @@ int64_t norm_partials_per_example(const dpsgd_layer& L, NormForm form) {
       const int64_t nt = ceil_div(L.T, kTile);
       return nt * (nt + 1) / 2;
     }
-    default:   // the k-major float32 kernel writes one partial per wave of a tile
-      return tiny_ok(L) ? 1 : k32_ok(L) ? 4 * mat_tile_count(L) : mat_tile_count(L);
+    default: return tiny_norm_ok(L) && !tr_tile_ok(L) ? 1 : mat_tile_count(L);
   }
 }
 
