@@ -67,6 +67,18 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return r;
 }
 
+// magic and shift such that n / d = umulhi(n, magic) >> shift for n < 2^31;
+// shift = -1 for d = 1. (magic = ceil(2^(31 + s) / d), s = ceil(log2 d).)
+inline void divide_magic(int64_t d, uint32_t* magic, int32_t* shift) {
+  *magic = 0;
+  *shift = -1;
+  if (d == 1) return;
+  int s = 1;
+  while ((INT64_C(1) << s) < d) ++s;
+  *magic = (uint32_t)(((((uint64_t)1) << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d);
+  *shift = s - 1;
+}
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ------------------------------------------------------------ host helpers
@@ -220,7 +232,10 @@ bool wide_tile_ok(const dpsgd_layer& L);
 void plan_wide_clip(const dpsgd_layer* layers, const int* idx, int n, int cus, TrClipPlan* plan);
 int launch_wide_clip(const dpsgd_layer* layers, const int* idx, int n, const float* factors,
                      float* const* outs, int accumulate, const TrClipPlan& plan, float* tail_ws,
-                     hipStream_t stream);
+                     bool ragged, hipStream_t stream);
+// The same tiles for layers that neither large-tile kernel takes: any T from 57
+// on, widths that are multiples of 8.
+bool wide_ragged_ok(const dpsgd_layer& L);
 int launch_tr_mat_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
                         float* partials, int64_t P, hipStream_t stream);
 
@@ -240,6 +255,9 @@ struct ClipPlan {
   size_t tr_offset;                              // their tail partials, from the partial base
   TrClipPlan wide;                               // layers on the 384x256-tile kernel
   size_t wide_offset;
+  TrClipPlan ragged;                             // layers on its instance for any T and widths
+  size_t ragged_offset;
+  bool use_ragged;                               // whether that instance is used at all
 };
 void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan);
 

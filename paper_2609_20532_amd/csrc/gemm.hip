@@ -255,7 +255,11 @@ constexpr int kAnyGroups = 8;
 int any_group(const dpsgd_layer& L) {
   return (any_flat(L) ? 0 : 1) + 2 * any_shape(L) + 4 * (any_slow(L) ? 1 : 0);
 }
-bool any_clip(const dpsgd_layer& L) { return !wide_tile_ok(L) && !tr_tile_ok(L) && !tiny_clip_ok(L); }
+// Whether the any-shape kernel takes the layer's clipped sum; ragged: the
+// launch sends its wide_ragged_ok layers to the 384x256 tiles.
+bool any_clip(const dpsgd_layer& L, bool ragged) {
+  return !wide_tile_ok(L) && !tr_tile_ok(L) && !(ragged && wide_ragged_ok(L)) && !tiny_clip_ok(L);
+}
 
 }  // namespace
 
@@ -271,12 +275,26 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   // the GPU on its own).
   const int cus = tr_cu_count();
   int tr_idx[kMaxLayersPerLaunch], n_tr = 0, wd_idx[kMaxLayersPerLaunch], n_wd = 0;
+  int rg_idx[kMaxLayersPerLaunch], n_rg = 0;
+  // The 384x256 tiles of the layers that they suit only with padding pay off
+  // once the launch holds enough work for its prologues and partial tiles:
+  // single layers of 8, 10, 12 and 13 GFLOP took 37.9, 38.9, 42.9 and 45.3 us
+  // against 35.3, 36.6, 42.9 and 41.1 on the any-shape kernel, layers of 29,
+  // 33, 48 and 164 GFLOP 72.9, 64.1, 79.5 and 180 against 79.2, 72.7, 98.9 and
+  // 300 us.
+  constexpr double kMinRaggedFlops = 2.0e10;
+  double ragged_flops = 0.0;
+  for (int l = 0; l < n_layers; ++l)
+    if (wide_ragged_ok(layers[l]))
+      ragged_flops += 2.0 * (double)(layers[l].B * layers[l].T) * (double)layers[l].d_in * (double)layers[l].d_out;
+  plan->use_ragged = ragged_flops >= kMinRaggedFlops;
   int any_idx[kAnyGroups][kMaxLayersPerLaunch], n_any[kAnyGroups] = {};
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
     if (wide_tile_ok(L)) wd_idx[n_wd++] = l;
     else if (tr_tile_ok(L)) tr_idx[n_tr++] = l;
-    else if (any_clip(L)) any_idx[any_group(L)][n_any[any_group(L)]++] = l;
+    else if (plan->use_ragged && wide_ragged_ok(L)) rg_idx[n_rg++] = l;
+    else if (any_clip(L, plan->use_ragged)) any_idx[any_group(L)][n_any[any_group(L)]++] = l;
   }
   constexpr int64_t kMinSlicesPerSplit = 4;
   constexpr int64_t kMaxSplits = 1024;
@@ -342,7 +360,7 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
     int64_t s = 1;
-    if (any_clip(L)) s = split_count(any_slices(L), chunk_of[any_group(L)]);
+    if (any_clip(L, plan->use_ragged)) s = split_count(any_slices(L), chunk_of[any_group(L)]);
     else if (tiny_clip_ok(L)) s = tiny_jobs(L);   // one partial per job of consecutive examples
     plan->splits[l] = (int)s;
     plan->partial_offset[l] = off;
@@ -352,14 +370,17 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   plan_wide_clip(layers, wd_idx, n_wd, cus, &plan->wide);
   plan->tr_offset = off;
   plan->wide_offset = off + round_up(plan->tr.tail_bytes, 256);
-  plan->partial_bytes = plan->wide_offset + round_up(plan->wide.tail_bytes, 256);
+  plan_wide_clip(layers, rg_idx, n_rg, cus, &plan->ragged);
+  plan->ragged_offset = plan->wide_offset + round_up(plan->wide.tail_bytes, 256);
+  plan->partial_bytes = plan->ragged_offset + round_up(plan->ragged.tail_bytes, 256);
 }
 
 int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factors,
                     float* const* grads, int accumulate, float* partial_base, const ClipPlan& plan,
                     hipStream_t stream) {
   // Group layers by kernel variant; each group is one grouped launch.
-  constexpr int kTr = kAnyGroups, kWide = kAnyGroups + 1, kTiny = kAnyGroups + 2, kClipGroups = kAnyGroups + 3;
+  constexpr int kTr = kAnyGroups, kWide = kAnyGroups + 1, kTiny = kAnyGroups + 2,
+                kRagged = kAnyGroups + 3, kClipGroups = kAnyGroups + 4;
   int idx[kClipGroups][kMaxLayersPerLaunch];
   float* outs[kClipGroups][kMaxLayersPerLaunch];
   int spl[kClipGroups][kMaxLayersPerLaunch];
@@ -367,7 +388,11 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factor
   int cnt[kClipGroups] = {};
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
-    const int g = wide_tile_ok(L) ? kWide : tr_tile_ok(L) ? kTr : tiny_clip_ok(L) ? kTiny : any_group(L);
+    const int g = wide_tile_ok(L)     ? kWide
+                  : tr_tile_ok(L)     ? kTr
+                  : plan.use_ragged && wide_ragged_ok(L) ? kRagged
+                  : tiny_clip_ok(L) ? kTiny
+                                    : any_group(L);
     const int k = cnt[g]++;
     idx[g][k] = l;
     spl[g][k] = plan.splits[l];
@@ -387,7 +412,13 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factor
     st = launch_wide_clip(layers, idx[kWide], cnt[kWide], factors, outs[kWide], accumulate, plan.wide,
                           reinterpret_cast<float*>(reinterpret_cast<char*>(partial_base) +
                                                    plan.wide_offset),
-                          stream);
+                          false, stream);
+  if (st == DPSGD_OK && cnt[kRagged])
+    st = launch_wide_clip(layers, idx[kRagged], cnt[kRagged], factors, outs[kRagged], accumulate,
+                          plan.ragged,
+                          reinterpret_cast<float*>(reinterpret_cast<char*>(partial_base) +
+                                                   plan.ragged_offset),
+                          true, stream);
   for (int g = 0; g < kAnyGroups; ++g)
     if (st == DPSGD_OK && cnt[g])
       st = launch_any_clip(layers, idx[g], cnt[g], factors, outs[g], spl[g], acc[g], stream);

@@ -111,7 +111,7 @@ struct AnyArgs {
   int64_t P;
 };
 
-// n / d for n < 2^31 with magic = ceil(2^(31 + s) / d), s = ceil(log2 d), shift = s - 1.
+// n / d for n < 2^31 (divide_magic).
 __device__ __forceinline__ uint32_t any_div(uint32_t n, uint32_t magic, int shift) {
   return shift < 0 ? n : __umulhi(n, magic) >> shift;
 }
@@ -639,18 +639,6 @@ __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs 
     }
 }
 
-void any_magic(int64_t d, uint32_t* magic, int32_t* shift) {
-  if (d == 1) {
-    *magic = 0;
-    *shift = -1;
-    return;
-  }
-  int s = 1;
-  while ((INT64_C(1) << s) < d) ++s;   // ceil(log2 d)
-  *magic = (uint32_t)(((((uint64_t)1) << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d);
-  *shift = s - 1;
-}
-
 template <typename TIn, int SHAPE, int MODE, bool SLOW>
 int launch_any(const dpsgd_layer* layers, const int* idx, int n, const float* factors,
                float* const* outs, const int* splits, const int* accumulate, const int64_t* cols,
@@ -675,7 +663,7 @@ int launch_any(const dpsgd_layer* layers, const int* idx, int n, const float* fa
       E.N = (int32_t)L.d_in;
       E.T = (int32_t)L.T;
       E.k_total = MODE == ANY_FLAT ? L.B * L.T : L.B * gpe;
-      any_magic(MODE == ANY_FLAT ? L.T : gpe, &E.magic, &E.shift);
+      divide_magic(MODE == ANY_FLAT ? L.T : gpe, &E.magic, &E.shift);
       E.tiles_n = (int32_t)any_tiles_n(L);
       E.wg_begin = (uint32_t)wgs;
       if (MODE == ANY_SUMSQ) {

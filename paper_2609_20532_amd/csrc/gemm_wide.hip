@@ -1,7 +1,9 @@
 // 384x256-tile transposed-operand MFMA GEMM for the clip-weighted sum of bf16
 // layers with d_in % 256 == 0 and d_out a multiple of 32 (the last row tile
 // may hold fewer than 384 rows: its G copies repeat the last valid 64-byte
-// column block, and the rows past d_out are not stored):
+// column block, and the rows past d_out are not stored), and, in a second
+// instance (RAGGED, below), of layers with any T >= 57 and widths that are
+// multiples of 8:
 //   out[m][n] = sum_k c(k) G[k][m] A[k][n],  k over the B*T rows, c = c_i of
 //   the example i = k / T (paper: Section 2.2, the clipped per-example
 //   gradients c_i g_i summed over the batch).
@@ -40,6 +42,14 @@
 //
 // Exact fp32 clip weights: the accumulator is kept in units of the current
 // example's factor and multiplied by c_prev / c_next at each example boundary.
+//
+// RAGGED. An example takes ceil(T / 64) slices; its last one copies and
+// multiplies only the 16-row groups that hold rows, and lanes past the last row
+// copy zeros, so T is padded to a multiple of 16. Column chunks past a width
+// repeat the row's last one; the elements they feed are not stored. Four
+// layers of a 768-wide block twice, B = 32, T = 183 (166 GFLOP): 243 us against
+// 375-417 on the any-shape kernel, whose 64-row slices cost several times the
+// instructions.
 #include "lds_dma.h"
 #include "mma.h"
 
@@ -70,6 +80,7 @@ constexpr int kWdLdsBytes = kWdStages * kWdStageBytes;   // 160 KB
 constexpr int kWdGCopies = kWdGBytes / 1024;             // 48
 constexpr int kWdCopies = kWdStageBytes / 1024 / kWdWaves;  // 5 per wave per slice
 constexpr int kWdTileElems = kWdTM * kWdTN;
+constexpr double kAnyVsWide = 0.62;   // the any-shape kernel's rate over this one's
 static_assert(kWdGCopies % kWdWaves == 0, "G copies split evenly over the waves");
 static_assert((kWdStageBytes / 1024) % kWdWaves == 0, "copies split evenly over the waves");
 static_assert(kWdWaves / kWdWavesN * kWdMB * 32 == kWdTM && kWdWavesN * kWdNB * 32 == kWdTN,
@@ -84,7 +95,7 @@ struct WdEntry {
   int32_t M, N, T;
   int32_t tiles_n;
   uint32_t tile_begin;
-  int64_t q_total;        // K slices of the layer (B * T / 32)
+  int64_t q_total;        // K slices of the layer
 };
 
 // Jobs [0, n_full) are whole tiles; the n_tail jobs after them split each
@@ -130,17 +141,17 @@ typedef f32x16_t WdAcc[kWdMB][kWdNB];
 // acc = sum over K slices [q0, q1) of tile (tm, tn) of layer E, weighted by the
 // clip factors; returns the factor the accumulator must be multiplied by.
 // ZA: slices of examples with factor 0 are copied from zeros.
-template <bool ZA>
+template <bool ZA, bool RAGGED>
 __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_t q1,
                             const float* factors, char* lds, WdAcc& acc) {
   const int M = E.M, N = E.N, T = E.T;
-  const int spe = T / kWdBK;
+  const int spe = RAGGED ? (T + kWdBK - 1) / kWdBK : T / kWdBK;   // slices per example
   // 32-column blocks of G inside the matrix (12 except in a ragged last row tile).
   const uint32_t nvb = (uint32_t)min(kWdTM / 32, (M - tm * kWdTM) / 32);
   const int lane = threadIdx.x & 63;
   const uint32_t wave_u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const char* Gt = static_cast<const char*>(E.G) + (int64_t)tm * kWdTM * 2;
-  const char* At = static_cast<const char*>(E.A) + (int64_t)tn * kWdTN * 2;
+  const char* Gt = static_cast<const char*>(E.G) + (RAGGED ? 0 : (int64_t)tm * kWdTM * 2);
+  const char* At = static_cast<const char*>(E.A) + (RAGGED ? 0 : (int64_t)tn * kWdTN * 2);
   const uint32_t lds_addr0 = lds_address(lds);
   typedef __attribute__((address_space(4))) const float const_float;
   const const_float* fac = (const const_float*)factors;
@@ -155,7 +166,17 @@ __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_
 #pragma unroll
   for (int p = 0; p < kWdCopies; ++p) {
     const uint32_t t = wave_u + (uint32_t)(kWdWaves * p);
-    if (p < kWdGCopies / kWdWaves) {
+    if (RAGGED) {
+      const bool gs = p < kWdGCopies / kWdWaves;
+      const uint32_t u = gs ? t : t - (uint32_t)kWdGCopies, per = gs ? 3u : 2u;
+      const uint32_t width = 2u * (uint32_t)(gs ? M : N);
+      const uint32_t col = (gs ? (uint32_t)tm * (kWdTM * 2u) : (uint32_t)tn * (kWdTN * 2u)) +
+                           64u * (4u * (u % per) + l_unit) + l_byte;
+      // (As plain C++ the product becomes a 64-bit multiply-add whose upper
+      // half stays allocated: five registers this loop does not have.)
+      asm("v_mul_lo_u32 %0, %1, %2" : "=v"(voff[p]) : "v"(4u * (u / per) + l_row), "s"(width));
+      voff[p] += min(col, width - 16u);
+    } else if (p < kWdGCopies / kWdWaves) {
       const uint32_t row = 4u * (t / 3u) + l_row, blk = 4u * (t % 3u) + l_unit;
       voff[p] = row * (uint32_t)M * 2u + 64u * min(blk, nvb - 1u) + l_byte;
     } else {
@@ -168,11 +189,39 @@ __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_
   const uint32_t zoff = 16u * (uint32_t)lane;
   const int64_t gslice = (int64_t)kWdBK * M * 2, aslice = (int64_t)kWdBK * N * 2;
 
-  int iex = (int)(q0 / spe);
-  int ils = (int)(q0 - (int64_t)iex * spe);
+  // Example and slice within it of the next slice to copy.
+  int iex = __builtin_amdgcn_readfirstlane((int)(q0 / spe));
+  int ils = __builtin_amdgcn_readfirstlane((int)(q0 - (int64_t)iex * spe));
   const char* zsrc = reinterpret_cast<const char*>(kWdZero);
   auto issue = [&](int64_t qq, int slot) {
     const bool zero = ZA && fac[iex] == 0.0f;
+    if (RAGGED) {
+      const uint32_t dst = lds_addr0 + (uint32_t)slot * kWdStageBytes;
+      const uint32_t row = (uint32_t)iex * (uint32_t)T + (uint32_t)(kWdBK * ils);
+      const char* gs = Gt + (uint64_t)row * (2u * (uint32_t)M);
+      const char* as = At + (uint64_t)row * (2u * (uint32_t)N);
+      const int nv = zero ? 0 : T - kWdBK * ils;   // rows of the example from the slice's first
+      const int n16 = (min(kWdBK, T - kWdBK * ils) + 15) & ~15;   // rows that are multiplied
+#pragma unroll
+      for (int p = 0; p < kWdCopies; ++p) {
+        const bool g = p < kWdGCopies / kWdWaves;
+        const int t = (int)wave_u + kWdWaves * p;
+        const int r0 = 4 * (g ? t / 3 : (t - kWdGCopies) / 2);   // the copy's first row
+        const uint32_t la = __builtin_amdgcn_readfirstlane(dst + 1024u * (uint32_t)t);
+        if (r0 + 4 <= nv) {
+          copy16_to_lds(g ? gs : as, voff[p], la);
+        } else if (r0 < n16) {
+          // The lane index is made here: kept across the loop it would push
+          // registers to scratch, whose reloads wait for every copy in flight.
+          uint32_t li;
+          asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(li));
+          if (r0 + (int)((li >> 2) & 3u) < nv) copy16_to_lds(g ? gs : as, voff[p], la);
+          else copy16_to_lds(zsrc, 16u * li, la);
+        }
+      }
+      if (++ils == spe) { ils = 0; ++iex; }
+      return;
+    }
     const char* gs = zero ? zsrc : Gt + qq * gslice;
     const char* as = zero ? zsrc : At + qq * aslice;
     const uint32_t dst = lds_addr0 + (uint32_t)slot * kWdStageBytes;
@@ -209,8 +258,7 @@ __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_
     for (int j = 0; j < kWdNB; ++j) acc[i][j] = f32x16_t{};
   float c_cur = 1.0f;
   bool started = false;
-  int ex = (int)(q0 / spe);
-  int ls = (int)(q0 - (int64_t)ex * spe);
+  int ex = iex, ls = ils;
 
   __syncthreads();   // the ring may still be read by a previous user
 
@@ -244,6 +292,7 @@ __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_
         started = true;
       }
     }
+    const int nks = RAGGED ? min(kWdBK / 16, (T - kWdBK * ls + 15) >> 4) : kWdBK / 16;
 
     const char* base = lds + (int)((q - q0) % kWdStages) * kWdStageBytes;
     const char* g0 = base + rg[0];
@@ -252,6 +301,7 @@ __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_
     const char* a1 = base + ra[1];
 #pragma unroll
     for (int ks = 0; ks < kWdBK / 16; ++ks) {
+      if (RAGGED && ks >= nks) break;   // uniform
       bf16x8_t b[kWdNB];
 #pragma unroll
       for (int j = 0; j < kWdNB; ++j) b[j] = wd_frag(a0, a1, ks * 4 * kWdAGroup + 256 * j);
@@ -269,25 +319,27 @@ __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_
 }
 
 // Writes scale * acc into a 384 x 256 row-major destination (row stride ld),
-// adding what is there when add; only the first nvb 32-row blocks (the rows
-// inside the matrix). Register v of block (i, j) in lane l is tile row
-// 32 (kWdMB wm + i) + 8 (v / 4) + 4 (l / 32) + v % 4, column 32 (kWdNB wn + j) + l % 32.
+// adding what is there when add; only the first rows x cols elements. Register
+// v of block (i, j) in lane l is tile row 32 (kWdMB wm + i) + 8 (v / 4) +
+// 4 (l / 32) + v % 4, column 32 (kWdNB wn + j) + l % 32.
 __device__ __forceinline__ void wd_store(float* dst, int64_t ld, const WdAcc& acc, float scale,
-                                         bool add, int nvb) {
+                                         bool add, int rows, int cols) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / kWdWavesN, wn = wave % kWdWavesN;
-  float* p0 = dst + (int64_t)(wm * kWdMB * 32 + 4 * (lane >> 5)) * ld + wn * kWdNB * 32 +
-              (lane & 31);
+  const int row0 = wm * kWdMB * 32 + 4 * (lane >> 5), col0 = wn * kWdNB * 32 + (lane & 31);
+  float* p0 = dst + (int64_t)row0 * ld + col0;
+  const bool edge = rows % 32 != 0 || cols < kWdTN;   // uniform
 #pragma unroll
   for (int i = 0; i < kWdMB; ++i) {
-    if (wm * kWdMB + i >= nvb) break;   // wave-uniform
+    if (32 * (wm * kWdMB + i) >= rows) break;   // wave-uniform
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      float* p = p0 + (int64_t)(32 * i + 8 * (v >> 2) + (v & 3)) * ld;
+      const int r = 32 * i + 8 * (v >> 2) + (v & 3);
+      float* p = p0 + (int64_t)r * ld;
 #pragma unroll
       for (int j = 0; j < kWdNB; ++j) {
         const float x = acc[i][j][v] * scale;
-        p[32 * j] = add ? p[32 * j] + x : x;
+        if (!edge || (row0 + r < rows && col0 + 32 * j < cols)) p[32 * j] = add ? p[32 * j] + x : x;
       }
     }
   }
@@ -297,6 +349,7 @@ __device__ __forceinline__ uint32_t wd_range_begin(uint32_t k, uint32_t Q, uint3
   return (uint32_t)(((uint64_t)Q * k) / w);
 }
 
+template <bool RAGGED>
 __global__ __launch_bounds__(kWdThreads, 1) void tgemm_wide_kernel(WdArgs args) {
   __shared__ __attribute__((aligned(1024))) char lds[kWdLdsBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -314,12 +367,13 @@ __global__ __launch_bounds__(kWdThreads, 1) void tgemm_wide_kernel(WdArgs args) 
   const WdEntry& E = args.L[l];
   const int tile = (int)(tile_g - E.tile_begin);
   const int tm = tile / E.tiles_n, tn = tile % E.tiles_n;
-  const int spe = E.T / kWdBK;
   const int64_t q_end = whole ? E.q_total : (int64_t)qb;
   int zero_here = 0;
   {
+    const int spe = (E.T + kWdBK - 1) / kWdBK;
     const int e1 = (int)((q_end - 1) / spe);
-    for (int e = (int)(qa / spe) + tid; e <= e1; e += kWdThreads) zero_here |= args.factors[e] == 0.0f;
+    for (int e = (int)(qa / spe) + tid; e <= e1; e += kWdThreads)
+      zero_here |= args.factors[e] == 0.0f;
   }
   int* flags = reinterpret_cast<int*>(lds);
   const bool wave_zero = __builtin_amdgcn_ballot_w64(zero_here != 0) != 0;
@@ -328,12 +382,14 @@ __global__ __launch_bounds__(kWdThreads, 1) void tgemm_wide_kernel(WdArgs args) 
   bool any_zero = false;
 #pragma unroll
   for (int w = 0; w < kWdWaves; ++w) any_zero |= flags[w] != 0;
-  const float c = any_zero ? wd_segment<true>(E, tm, tn, qa, q_end, args.factors, lds, acc)
-                           : wd_segment<false>(E, tm, tn, qa, q_end, args.factors, lds, acc);
+  const float c =
+      any_zero ? wd_segment<true, RAGGED>(E, tm, tn, qa, q_end, args.factors, lds, acc)
+               : wd_segment<false, RAGGED>(E, tm, tn, qa, q_end, args.factors, lds, acc);
   float* dst = whole ? E.out + (int64_t)tm * kWdTM * E.N + tn * kWdTN
                      : args.partials + (int64_t)(job - args.n_full) * kWdTileElems;
   const int64_t ld = whole ? (int64_t)E.N : (int64_t)kWdTN;
-  wd_store(dst, ld, acc, c, whole && args.accumulate, min(kWdTM / 32, (E.M - tm * kWdTM) / 32));
+  wd_store(dst, ld, acc, c, whole && args.accumulate, min(kWdTM, E.M - tm * kWdTM),
+           min(kWdTN, E.N - tn * kWdTN));
 }
 
 // Adds the tail_w partials of every tail tile in range order (deterministic)
@@ -351,7 +407,7 @@ __global__ __launch_bounds__(256) void wide_fixup_kernel(WdArgs args) {
   const int tm = tile / E.tiles_n, tn = tile % E.tiles_n;
   const int e = (int)(blockIdx.x % kChunks) * 1024 + threadIdx.x * 4;
   const int r = e / kWdTN, c = e % kWdTN;
-  if (tm * kWdTM + r >= E.M) return;   // rows past d_out of a ragged last row tile
+  if (tm * kWdTM + r >= E.M || tn * kWdTN + c >= E.N) return;   // past the edge of the matrix
   const float* src = args.partials + (int64_t)t_local * args.tail_w * kWdTileElems + e;
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int k = 0; k < args.tail_w; ++k) {
@@ -386,13 +442,26 @@ bool wide_tile_ok(const dpsgd_layer& L) {
          L.d_in <= (INT64_C(1) << 24) && L.d_out <= (INT64_C(1) << 24);
 }
 
+bool wide_ragged_ok(const dpsgd_layer& L) {
+  // The widths' 16-byte chunks must not straddle rows; T as any_flat's rule
+  // says (weights on the accumulator, at least four groups an example). The
+  // padded tile area is compared with the any-shape kernel's at the rates both
+  // sustain (4088 x 2040 at B = 8, T = 1000: 874 and 578 TFLOP/s; 6400 x 1600 at
+  // B = 16, T = 500: 910 and 545).
+  if (L.dtype != DPSGD_BF16 || wide_tile_ok(L) || tr_tile_ok(L) || any_flat(L)) return false;
+  if (L.d_in % 8 != 0 || L.d_out % 8 != 0 || L.d_in > (INT64_C(1) << 24) || L.d_out > (INT64_C(1) << 24))
+    return false;
+  const double wide = (double)wide_tiles_m(L) * (double)ceil_div(L.d_in, kWdTN) * kWdTileElems;
+  return wide * kAnyVsWide <= (double)any_tiles(L) * any_tile_area(L);
+}
+
 void plan_wide_clip(const dpsgd_layer* layers, const int* idx, int n, int cus, TrClipPlan* plan) {
   int64_t tiles = 0, Q = -1;
   bool uniform = true;
   for (int k = 0; k < n; ++k) {
     const dpsgd_layer& L = layers[idx[k]];
-    tiles += wide_tiles_m(L) * (L.d_in / kWdTN);
-    const int64_t q = L.B * (L.T / kWdBK);
+    tiles += wide_tiles_m(L) * (ceil_div(L.d_in, kWdTN));
+    const int64_t q = L.B * ceil_div(L.T, kWdBK);
     if (Q >= 0 && q != Q) uniform = false;
     Q = q;
   }
@@ -416,7 +485,7 @@ void plan_wide_clip(const dpsgd_layer* layers, const int* idx, int n, int cus, T
 
 int launch_wide_clip(const dpsgd_layer* layers, const int* idx, int n, const float* factors,
                      float* const* outs, int accumulate, const TrClipPlan& plan, float* tail_ws,
-                     hipStream_t stream) {
+                     bool ragged, hipStream_t stream) {
   if (n > kMaxLayersPerLaunch) return DPSGD_ERR_INVALID_ARG;
   WdArgs args{};
   args.n = n;
@@ -438,15 +507,18 @@ int launch_wide_clip(const dpsgd_layer* layers, const int* idx, int n, const flo
     E.M = (int32_t)L.d_out;
     E.N = (int32_t)L.d_in;
     E.T = (int32_t)L.T;
-    E.tiles_n = (int32_t)(L.d_in / kWdTN);
+    E.tiles_n = (int32_t)(ceil_div(L.d_in, kWdTN));
     E.tile_begin = (uint32_t)tb;
-    E.q_total = L.B * (L.T / kWdBK);
+    E.q_total = L.B * ceil_div(L.T, kWdBK);
     tb += wide_tiles_m(L) * E.tiles_n;
   }
   const int64_t jobs = plan.n_full + plan.n_tail;
   if (jobs <= 0) return DPSGD_OK;
   if (jobs > 0x7FFFFFFF) return DPSGD_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(tgemm_wide_kernel, dim3((uint32_t)jobs), dim3(kWdThreads), 0, stream, args);
+  if (ragged)
+    hipLaunchKernelGGL(tgemm_wide_kernel<true>, dim3((uint32_t)jobs), dim3(kWdThreads), 0, stream, args);
+  else
+    hipLaunchKernelGGL(tgemm_wide_kernel<false>, dim3((uint32_t)jobs), dim3(kWdThreads), 0, stream, args);
   if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
   if (plan.n_tail > 0) {
     const int64_t wgs = (plan.n_tiles - plan.n_full) * (kWdTileElems / 1024);

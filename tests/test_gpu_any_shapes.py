@@ -1,6 +1,6 @@
 """Clipped sums and materialised norms at the edges of the any-shape kernel
 (tiles of 128 x 128, and of 64 x 192 for d_out <= 64; 16-byte row loads;
-16-row groups of an example), against the float64 oracle, and what it does with
+16-row groups of an example) and of the 384 x 256 tiles with padding, against the float64 oracle, and what it does with
 infinities in float32 (whose three bf16 parts do not exist)."""
 
 import math
@@ -26,6 +26,10 @@ CASES = [
     (wl.BF16, 4, [(1, 130, 67), (17, 192, 9), (50, 129, 200)]),          # weight on the operand
     (wl.BF16, 3, [(65, 7, 300), (65, 300, 7), (20, 2, 300), (3, 1, 1)]),    # rows below 16 bytes
     (wl.BF16, 1, [(512, 72, 24)]),
+    # at least 20 GFLOP in all: the 384 x 256 tiles with padding (last row, column
+    # and K slice partly filled; T one row past a slice and one row short of one)
+    (wl.BF16, 3, [(1025, 1608, 2000), (1000, 512, 392)]),
+    (wl.BF16, 5, [(191, 2040, 3000), (257, 776, 1544), (130, 256, 4104)]),
 ]
 
 
@@ -39,7 +43,7 @@ def _host_layer(B, T, d_in, d_out, dtype, seed, tensor_id):
 
 
 def _bound(dtype, T, d_in, d_out):
-    # float32: 24-bit products, a few thousand float32 additions at most.
+    # float32 and float32 weights: a few thousand float32 additions at most.
     # bf16 with the weight on the operand: one rounding (2^-9) per term.
     if dtype == wl.F32 or d_in * d_out <= 512:
         return 2e-6
