@@ -331,13 +331,28 @@ int dpsgd_clip_accumulate_multi(const dpsgd_layer* layers, int32_t n_layers,
   float* factors = static_cast<float*>(workspace);
   float* partial_base = reinterpret_cast<float*>(
       static_cast<char*>(workspace) + round_up((size_t)B * sizeof(float), kFactorBytesAlign));
-  st = launch_clip_factors(norms_sq, B, C, factors, factors_out, mask_out, s);
-  if (st != DPSGD_OK) return st;
+  ClipWeights weights;
+  // (An output over the norms themselves is written before the sums start.)
+  const auto overlaps = [&](const void* p, size_t bytes) {
+    const char *a = static_cast<const char*>(p), *n = reinterpret_cast<const char*>(norms_sq);
+    return p && a < n + (size_t)B * sizeof(float) && n < a + bytes;
+  };
+  if (clip_from_norms(layers, n_layers) && !overlaps(factors_out, (size_t)B * sizeof(float)) &&
+      !overlaps(mask_out, (size_t)B)) {
+    weights.norms_sq = norms_sq;
+    weights.C = C;
+    weights.factors_out = factors_out;
+    weights.mask_out = mask_out;
+  } else {
+    weights.factors = factors;
+    st = launch_clip_factors(norms_sq, B, C, factors, factors_out, mask_out, s);
+    if (st != DPSGD_OK) return st;
+  }
   for (int32_t base = 0; base < n_layers; base += kMaxLayersPerLaunch) {
     const int m = n_layers - base < kMaxLayersPerLaunch ? n_layers - base : kMaxLayersPerLaunch;
     ClipPlan plan;
     plan_clip(layers + base, m, &plan);
-    st = launch_clip_sum(layers + base, m, factors, grads + base, accumulate ? 1 : 0,
+    st = launch_clip_sum(layers + base, m, weights, grads + base, accumulate ? 1 : 0,
                          partial_base, plan, s);
     if (st != DPSGD_OK) return st;
   }
@@ -398,12 +413,13 @@ int dpsgd_clipped_sum_multi(const dpsgd_layer* layers, int32_t n_layers, int32_t
                              stores.data(), partials, p.norms.P, s);
     if (st != DPSGD_OK) return st;
   }
-  st = launch_norms_reduce(partials, p.norms.P, B, norms_sq, 0, s);
+  st = launch_norms_reduce_factors(partials, p.norms.P, B, norms_sq, C, factors, factors_out,
+                                   mask_out, s);
   if (st != DPSGD_OK) return st;
 
-  // Factors, then the clipped sums.
-  st = launch_clip_factors(norms_sq, B, C, factors, factors_out, mask_out, s);
-  if (st != DPSGD_OK) return st;
+  // The clipped sums.
+  ClipWeights weights;
+  weights.factors = factors;
   const int n_ot = (int)p.other.size();
   std::vector<float*> other_grads;
   for (int l : p.other) other_grads.push_back(grads[l]);
@@ -411,7 +427,7 @@ int dpsgd_clipped_sum_multi(const dpsgd_layer* layers, int32_t n_layers, int32_t
     const int m = n_ot - base < kMaxLayersPerLaunch ? n_ot - base : kMaxLayersPerLaunch;
     ClipPlan plan;
     plan_clip(p.other_layers.data() + base, m, &plan);
-    st = launch_clip_sum(p.other_layers.data() + base, m, factors, other_grads.data() + base,
+    st = launch_clip_sum(p.other_layers.data() + base, m, weights, other_grads.data() + base,
                          accumulate ? 1 : 0, clip_partials, plan, s);
     if (st != DPSGD_OK) return st;
   }

@@ -79,6 +79,21 @@ inline void divide_magic(int64_t d, uint32_t* magic, int32_t* shift) {
   *shift = s - 1;
 }
 
+// Clip factor of a squared norm: min(1, C / n); a NaN norm gives a NaN factor.
+__device__ __forceinline__ float clip_factor(float norm_sq, float C) {
+  const float n = sqrtf(norm_sq);
+  return n > C ? C / n : (n == n ? 1.0f : n);
+}
+
+// Writes example i's factor and clip mask where asked for.
+__device__ __forceinline__ void write_factor(float norm_sq, float C, int64_t i, float* factors,
+                                             float* factors_out, uint8_t* mask_out) {
+  const float c = clip_factor(norm_sq, C);
+  if (factors) factors[i] = c;
+  if (factors_out) factors_out[i] = c;
+  if (mask_out) mask_out[i] = sqrtf(norm_sq) > C ? 1 : 0;
+}
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ------------------------------------------------------------ host helpers
@@ -108,6 +123,10 @@ int launch_norm_partials(const dpsgd_layer* layers, const NormForm* forms, int n
                          hipStream_t stream);
 int launch_norms_reduce(const float* partials, int64_t P, int64_t B, float* norms_sq,
                         int accumulate, hipStream_t stream);
+// The same sums, and the clip factors of them (factors_out, mask_out may be null).
+int launch_norms_reduce_factors(const float* partials, int64_t P, int64_t B, float* norms_sq,
+                                float C, float* factors, float* factors_out, uint8_t* mask_out,
+                                hipStream_t stream);
 
 // Stored per-example gradients of layers with a narrow side (skinny.hip).
 // skinny_ok: eligible (narrow side <= kSkinnyMaxRank, wide side a multiple of
@@ -174,8 +193,18 @@ double any_tile_area(const dpsgd_layer& L);
 int any_workgroups_per_cu();
 bool any_slow(const dpsgd_layer& L);   // widths below 16 bytes and others: a kernel of its own
 int any_ex_per_job(const dpsgd_layer& L);   // examples per materialised-norm job
-// The layers of one launch have one dtype, shape, any_slow and (clip) weight mode.
-int launch_any_clip(const dpsgd_layer* layers, const int* idx, int n, const float* factors,
+// Where a clipped sum's weights come from: the factors, or (any_flat layers
+// only) the squared norms, from which the kernel forms them and writes them to
+// factors_out and mask_out.
+struct ClipWeights {
+  const float* factors = nullptr;
+  const float* norms_sq = nullptr;
+  float C = 0.0f;
+  float* factors_out = nullptr;
+  uint8_t* mask_out = nullptr;
+};
+// The layers of one launch have one dtype, any_slow and (clip) weight mode.
+int launch_any_clip(const dpsgd_layer* layers, const int* idx, int n, const ClipWeights& weights,
                     float* const* outs, const int* splits, const int* accumulate,
                     hipStream_t stream);
 int launch_any_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
@@ -258,10 +287,14 @@ struct ClipPlan {
   TrClipPlan ragged;                             // layers on its instance for any T and widths
   size_t ragged_offset;
   bool use_ragged;                               // whether that instance is used at all
+  bool merge_shapes;                             // any-shape layers of both shapes share launches
 };
 void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan);
 
-int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factors,
+// Small launches of any_flat layers form the clip factors themselves: whether
+// the plan allows it for the layers of a whole call.
+bool clip_from_norms(const dpsgd_layer* layers, int n_layers);
+int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const ClipWeights& weights,
                     float* const* grads, int accumulate, float* partial_base,
                     const ClipPlan& plan, hipStream_t stream);
 

@@ -251,10 +251,19 @@ int64_t mat_tile_count(const dpsgd_layer& L) {
 namespace {
 
 // Launch of the any-shape kernel that takes a layer (one dtype in a call).
+// Both tile shapes share a launch when the launch is short (a launch costs
+// about 4 us) and have one each when it is long: their slices differ in cost,
+// and a plan of its own fills the rounds better (the convolutions of WRN-16-4,
+// B = 256: 1.46 against 1.42 ms, and half the partial sums).
 constexpr int kAnyGroups = 8;
-int any_group(const dpsgd_layer& L) {
-  return (any_flat(L) ? 0 : 1) + 2 * any_shape(L) + 4 * (any_slow(L) ? 1 : 0);
+constexpr double kMergeFlops = 1.0e10;
+int any_group(const dpsgd_layer& L, bool merge) {
+  return (any_flat(L) ? 0 : 1) + 2 * (any_slow(L) ? 1 : 0) + (merge ? 0 : 4 * any_shape(L));
 }
+double clip_flops(const dpsgd_layer& L) {
+  return 2.0 * (double)(L.B * L.T) * (double)L.d_in * (double)L.d_out;
+}
+
 // Whether the any-shape kernel takes the layer's clipped sum; ragged: the
 // launch sends its wide_ragged_ok layers to the 384x256 tiles.
 bool any_clip(const dpsgd_layer& L, bool ragged) {
@@ -285,16 +294,19 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   constexpr double kMinRaggedFlops = 2.0e10;
   double ragged_flops = 0.0;
   for (int l = 0; l < n_layers; ++l)
-    if (wide_ragged_ok(layers[l]))
-      ragged_flops += 2.0 * (double)(layers[l].B * layers[l].T) * (double)layers[l].d_in * (double)layers[l].d_out;
+    if (wide_ragged_ok(layers[l])) ragged_flops += clip_flops(layers[l]);
   plan->use_ragged = ragged_flops >= kMinRaggedFlops;
+  double any_flops = 0.0;
+  for (int l = 0; l < n_layers; ++l)
+    if (any_clip(layers[l], plan->use_ragged)) any_flops += clip_flops(layers[l]);
+  const bool merge = plan->merge_shapes = any_flops <= kMergeFlops;
   int any_idx[kAnyGroups][kMaxLayersPerLaunch], n_any[kAnyGroups] = {};
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
     if (wide_tile_ok(L)) wd_idx[n_wd++] = l;
     else if (tr_tile_ok(L)) tr_idx[n_tr++] = l;
     else if (plan->use_ragged && wide_ragged_ok(L)) rg_idx[n_rg++] = l;
-    else if (any_clip(L, plan->use_ragged)) any_idx[any_group(L)][n_any[any_group(L)]++] = l;
+    else if (any_clip(L, plan->use_ragged)) any_idx[any_group(L, merge)][n_any[any_group(L, merge)]++] = l;
   }
   constexpr int64_t kMinSlicesPerSplit = 4;
   constexpr int64_t kMaxSplits = 1024;
@@ -318,7 +330,7 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
     const dpsgd_layer& L0 = layers[any_idx[g][0]];
     const int64_t slots = (int64_t)any_workgroups_per_cu() * cus;
     const double rate = L0.dtype == DPSGD_F32 ? 1.4e14 : 6.0e14;
-    const double t_slice = 2.0 * any_tile_area(L0) * any_slice_rows(L0) * (double)slots / rate;
+    const double t_slice = 2.0 * 128 * 128 * any_slice_rows(L0) * (double)slots / rate;
     constexpr double kHbm = 4.0e12;
     int64_t q_max = 1;
     for (int k = 0; k < n_any[g]; ++k) q_max = std::max(q_max, any_slices(layers[any_idx[g][k]]));
@@ -360,7 +372,7 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
     int64_t s = 1;
-    if (any_clip(L, plan->use_ragged)) s = split_count(any_slices(L), chunk_of[any_group(L)]);
+    if (any_clip(L, plan->use_ragged)) s = split_count(any_slices(L), chunk_of[any_group(L, merge)]);
     else if (tiny_clip_ok(L)) s = tiny_jobs(L);   // one partial per job of consecutive examples
     plan->splits[l] = (int)s;
     plan->partial_offset[l] = off;
@@ -375,7 +387,21 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   plan->partial_bytes = plan->ragged_offset + round_up(plan->ragged.tail_bytes, 256);
 }
 
-int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factors,
+bool clip_from_norms(const dpsgd_layer* layers, int n_layers) {
+  // Forming a factor takes about 30 instructions a slice and lane, next to the
+  // 150 of a float32 slice; a launch for the factors takes about 4 us with its
+  // gap. The whole call has to be one launch of any_flat layers.
+  constexpr double kMostFlops = 2.0e9;   // about 20 us of the kernel
+  double flops = 0.0;
+  for (int l = 0; l < n_layers; ++l) {
+    const dpsgd_layer& L = layers[l];
+    if (!any_clip(L, true) || any_group(L, true) != any_group(layers[0], true) || !any_flat(L)) return false;
+    flops += clip_flops(L);
+  }
+  return n_layers <= kMaxLayersPerLaunch && flops <= kMostFlops;
+}
+
+int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const ClipWeights& weights,
                     float* const* grads, int accumulate, float* partial_base, const ClipPlan& plan,
                     hipStream_t stream) {
   // Group layers by kernel variant; each group is one grouped launch.
@@ -392,7 +418,7 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factor
                   : tr_tile_ok(L)     ? kTr
                   : plan.use_ragged && wide_ragged_ok(L) ? kRagged
                   : tiny_clip_ok(L) ? kTiny
-                                    : any_group(L);
+                                    : any_group(L, plan.merge_shapes);
     const int k = cnt[g]++;
     idx[g][k] = l;
     spl[g][k] = plan.splits[l];
@@ -402,6 +428,7 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factor
                      : grads[l];
     acc[g][k] = accumulate;
   }
+  const float* factors = weights.factors;
   int st = DPSGD_OK;
   if (cnt[kTr])
     st = launch_tr_clip(layers, idx[kTr], cnt[kTr], factors, outs[kTr], accumulate, plan.tr,
@@ -421,7 +448,7 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factor
                           true, stream);
   for (int g = 0; g < kAnyGroups; ++g)
     if (st == DPSGD_OK && cnt[g])
-      st = launch_any_clip(layers, idx[g], cnt[g], factors, outs[g], spl[g], acc[g], stream);
+      st = launch_any_clip(layers, idx[g], cnt[g], weights, outs[g], spl[g], acc[g], stream);
   if (st == DPSGD_OK && cnt[kTiny])
     st = launch_tiny_group<uint16_t, EPI_STORE>(layers, idx[kTiny], cnt[kTiny], factors, outs[kTiny], spl[kTiny], acc[kTiny],
                                                 nullptr, nullptr, 0, stream);
@@ -454,19 +481,17 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const float* factor
 int launch_mat_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
                      float* partials, int64_t P, hipStream_t stream) {
   const bool bf16 = layers[idx[0]].dtype == DPSGD_BF16;
-  int ib[256], it[256], ia[4][256], nb = 0, nt = 0, na[4] = {};
+  int ib[256], it[256], ia[2][256], nb = 0, nt = 0, na[2] = {0, 0};
   for (int k = 0; k < n; ++k) {
     const dpsgd_layer& L = layers[idx[k]];
+    const int g = any_slow(L) ? 1 : 0;
     if (tr_tile_ok(L)) ib[nb++] = idx[k];
     else if (tiny_norm_ok(L)) it[nt++] = idx[k];
-    else {
-      const int g = any_shape(L) + 2 * (any_slow(L) ? 1 : 0);
-      ia[g][na[g]++] = idx[k];
-    }
+    else ia[g][na[g]++] = idx[k];
   }
   int st = DPSGD_OK;
   if (nb) st = launch_tr_mat_norms(layers, ib, nb, cols, partials, P, stream);
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < 2; ++g)
     if (st == DPSGD_OK && na[g]) st = launch_any_norms(layers, ia[g], na[g], cols, partials, P, stream);
   if (st == DPSGD_OK && nt)
     st = bf16 ? launch_tiny_group<uint16_t, EPI_SUMSQ>(layers, it, nt, nullptr, nullptr, nullptr,

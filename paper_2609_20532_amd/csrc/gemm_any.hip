@@ -98,6 +98,7 @@ struct AnyEntry {
   int32_t partial_col;   // norms: first partial slot (one per tile)
   int32_t accumulate;    // sums, splits == 1: add to grad
   int32_t ex_per_job;    // norms: consecutive examples of one job
+  int32_t shape;
   uint32_t magic;        // FLAT: divides a row by T; otherwise a group by ceil(T / 16)
   int32_t shift;         // -1: the divisor is 1
 };
@@ -109,6 +110,13 @@ struct AnyArgs {
   const float* factors;
   float* partials;       // norms
   int64_t P;
+  // FLAT without `factors`: the weights come from the squared norms, and the
+  // workgroups after the jobs write them out (either output may be null).
+  const float* norms_sq;
+  float C;
+  float* factors_out;
+  uint8_t* mask_out;
+  uint32_t jobs;
 };
 
 // n / d for n < 2^31 (divide_magic).
@@ -152,7 +160,8 @@ __device__ __forceinline__ uint4 any_shift(uint4 v, int n) {
 template <int MB, int NB>
 __device__ __forceinline__ void recompute_f32(const float* G, const float* A, int M, int N,
                                               int m_base, int n_base, int64_t r0, int64_t r1, int T,
-                                              const float* factors, f32x16_t (&acc)[MB][NB]) {
+                                              const float* factors, const float* norms_sq,
+                                              float clip, f32x16_t (&acc)[MB][NB]) {
   const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31;
 #pragma unroll
   for (int a = 0; a < MB; ++a)
@@ -162,6 +171,7 @@ __device__ __forceinline__ void recompute_f32(const float* G, const float* A, in
     const int64_t row = r + h;
     float c = 1.0f;
     if (factors && row < r1) c = factors[row / T];
+    if (norms_sq && row < r1) c = clip_factor(norms_sq[row / T], clip);
     const bool use = row < r1 && c != 0.0f;
     float g[MB], x[NB];
 #pragma unroll
@@ -182,27 +192,16 @@ __device__ __forceinline__ void recompute_f32(const float* G, const float* A, in
   }
 }
 
-// SLOW: layers whose rows the 32-bit lane offsets or the 16-byte loads do not
-// suit (any_slow).
-template <typename TIn, int SHAPE, int MODE, bool SLOW>
-__global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs args) {
+// One job of a launch. SLOW: layers whose rows the 32-bit lane offsets or the
+// 16-byte loads do not suit (any_slow). NSQ (FLAT): see AnyArgs::norms_sq.
+// lds: two stages; ended (norms): [2][groups of a slice][4], the four waves'
+// sums of the examples that ended in a slice (at most one per group), added
+// and stored after the slice's barrier.
+template <typename TIn, int SHAPE, int MODE, bool SLOW, bool NSQ>
+__device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, char* lds,
+                                        float (*ended)[4][4]) {
   using C = AnyCfg<TIn, SHAPE>;
   constexpr int ES = (int)sizeof(TIn);
-  __shared__ __attribute__((aligned(1024))) char lds[2 * C::kStageBytes];
-  // Norms: the four waves' sums of the examples that ended in a slice, added
-  // and stored after the slice's barrier. (At most one example ends per group.)
-  __shared__ float ended[2][C::kGroups][4];
-
-  int l = 0;
-  {
-    int lo = 0, hi = args.n - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (args.L[mid].wg_begin <= blockIdx.x) lo = mid; else hi = mid - 1;
-    }
-    l = lo;
-  }
-  const AnyEntry& E = args.L[l];
   const int M = E.M, N = E.N, T = E.T;
   const uint32_t magic = E.magic;
   const int shift = E.shift;
@@ -308,7 +307,8 @@ __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs 
       }
       S.nv[gi] = nv;
       if (MODE == ANY_FLAT)
-        S.w[gi] = args.factors[any_div((uint32_t)min(row0 + rl, rows_total - 1), magic, shift)];
+        S.w[gi] = (NSQ ? args.norms_sq : args.factors)[any_div(
+            (uint32_t)min(row0 + rl, rows_total - 1), magic, shift)];
       if constexpr (SLOW) {
         const int64_t row = min(row0 + rl, rows_total - 1);
 #pragma unroll
@@ -361,6 +361,10 @@ __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs 
 
   auto commit = [&](Slice& S, int buf) {
     char* dst = lds + buf * C::kStageBytes + woff;
+    if (NSQ) {
+#pragma unroll
+      for (int gi = 0; gi < C::kWaveGroups; ++gi) S.w[gi] = clip_factor(S.w[gi], args.C);
+    }
     // Overrunning loads of edge tiles (uniform branches).
     if (g_edge && (!SLOW || M >= C::kE)) {
 #pragma unroll
@@ -534,7 +538,8 @@ __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs 
       if (inside && !(s < __builtin_inff())) {
         recompute_f32<C::kMB, C::kNB>(reinterpret_cast<const float*>(Gb),
                                       reinterpret_cast<const float*>(Ab), M, N, m_base, n_base,
-                                      (int64_t)ex * T, (int64_t)(ex + 1) * T, T, nullptr, acc);
+                                      (int64_t)ex * T, (int64_t)(ex + 1) * T, T, nullptr, nullptr,
+                                      0.f, acc);
         // Outside the matrix 0 times an infinity is no zero.
 #pragma unroll
         for (int a = 0; a < C::kMB; ++a)
@@ -617,7 +622,8 @@ __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs 
     if (__builtin_amdgcn_ballot_w64(bad != bad) != 0)
       recompute_f32<C::kMB, C::kNB>(reinterpret_cast<const float*>(Gb),
                                     reinterpret_cast<const float*>(Ab), M, N, m_base, n_base, k0, k1,
-                                    T, args.factors, acc);
+                                    T, NSQ ? nullptr : args.factors, NSQ ? args.norms_sq : nullptr,
+                                    args.C, acc);
   }
   // Element v of block (a, b) in lane l: row 32 a + 8 (v / 4) + 4 (l / 32) +
   // v % 4, column 32 b + l % 32.
@@ -639,8 +645,30 @@ __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs 
     }
 }
 
-template <typename TIn, int SHAPE, int MODE, bool SLOW>
-int launch_any(const dpsgd_layer* layers, const int* idx, int n, const float* factors,
+// Layers of both shapes run in one launch (their LDS is the same size).
+template <typename TIn, int MODE, bool SLOW, bool NSQ>
+__global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs args) {
+  using C = AnyCfg<TIn, 0>;
+  static_assert(C::kStageBytes == AnyCfg<TIn, 1>::kStageBytes && C::kGroups <= 4, "one LDS layout");
+  __shared__ __attribute__((aligned(1024))) char lds[2 * C::kStageBytes];
+  __shared__ float ended[2][4][4];
+  if (NSQ && blockIdx.x >= args.jobs) {
+    const int i = (int)(blockIdx.x - args.jobs) * kThreads + (int)threadIdx.x;
+    if (i < args.B) write_factor(args.norms_sq[i], args.C, i, nullptr, args.factors_out, args.mask_out);
+    return;
+  }
+  int lo = 0, hi = args.n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (args.L[mid].wg_begin <= blockIdx.x) lo = mid; else hi = mid - 1;
+  }
+  const AnyEntry& E = args.L[lo];
+  if (E.shape) any_job<TIn, 1, MODE, SLOW, NSQ>(args, E, lds, ended);
+  else any_job<TIn, 0, MODE, SLOW, NSQ>(args, E, lds, ended);
+}
+
+template <typename TIn, int MODE, bool SLOW, bool NSQ>
+int launch_any(const dpsgd_layer* layers, const int* idx, int n, const ClipWeights& weights,
                float* const* outs, const int* splits, const int* accumulate, const int64_t* cols,
                float* partials, int64_t P, hipStream_t stream) {
   for (int base = 0; base < n; base += kMaxLayersPerLaunch) {
@@ -648,7 +676,12 @@ int launch_any(const dpsgd_layer* layers, const int* idx, int n, const float* fa
     AnyArgs args{};
     args.n = m;
     args.B = (int32_t)layers[idx[base]].B;
-    args.factors = factors;
+    args.factors = weights.factors;
+    args.norms_sq = weights.norms_sq;
+    args.C = weights.C;
+    // One of the call's launches writes the factors out.
+    args.factors_out = base == 0 ? weights.factors_out : nullptr;
+    args.mask_out = base == 0 ? weights.mask_out : nullptr;
     args.partials = partials;
     args.P = P;
     int64_t wgs = 0;
@@ -659,6 +692,7 @@ int launch_any(const dpsgd_layer* layers, const int* idx, int n, const float* fa
       const int64_t gpe = ceil_div(L.T, 16);
       E.G = L.G;
       E.A = L.A;
+      E.shape = any_shape(L);
       E.M = (int32_t)L.d_out;
       E.N = (int32_t)L.d_in;
       E.T = (int32_t)L.T;
@@ -678,8 +712,10 @@ int launch_any(const dpsgd_layer* layers, const int* idx, int n, const float* fa
         wgs += any_tiles(L) * E.splits;
       }
     }
+    args.jobs = (uint32_t)wgs;
+    if (NSQ && (args.factors_out || args.mask_out)) wgs += ceil_div(args.B, kThreads);
     if (wgs > 0x7FFFFFFF) return DPSGD_ERR_INVALID_ARG;
-    hipLaunchKernelGGL((tgemm_any_kernel<TIn, SHAPE, MODE, SLOW>), dim3((uint32_t)wgs), dim3(kThreads), 0,
+    hipLaunchKernelGGL((tgemm_any_kernel<TIn, MODE, SLOW, NSQ>), dim3((uint32_t)wgs), dim3(kThreads), 0,
                        stream, args);
     if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
   }
@@ -727,33 +763,31 @@ bool any_slow(const dpsgd_layer& L) {
   return std::min(L.d_in, L.d_out) * es < 16 || std::max(L.d_in, L.d_out) * es >= (INT64_C(1) << 28);
 }
 
-int launch_any_clip(const dpsgd_layer* layers, const int* idx, int n, const float* factors,
+int launch_any_clip(const dpsgd_layer* layers, const int* idx, int n, const ClipWeights& weights,
                     float* const* outs, const int* splits, const int* accumulate,
                     hipStream_t stream) {
   const dpsgd_layer& L = layers[idx[0]];
-  const bool narrow = any_shape(L) == 1, sh = any_slow(L);
-#define DPSGD_ANY(T_, S_, M_)                                                                        \
-  (sh ? launch_any<T_, S_, M_, true>(layers, idx, n, factors, outs, splits, accumulate, nullptr,    \
-                                     nullptr, 0, stream)                                            \
-      : launch_any<T_, S_, M_, false>(layers, idx, n, factors, outs, splits, accumulate, nullptr,   \
-                                      nullptr, 0, stream))
-  if (L.dtype == DPSGD_F32) return narrow ? DPSGD_ANY(float, 1, ANY_FLAT) : DPSGD_ANY(float, 0, ANY_FLAT);
-  if (any_flat(L)) return narrow ? DPSGD_ANY(uint16_t, 1, ANY_FLAT) : DPSGD_ANY(uint16_t, 0, ANY_FLAT);
-  return narrow ? DPSGD_ANY(uint16_t, 1, ANY_EX) : DPSGD_ANY(uint16_t, 0, ANY_EX);
+  const bool slow = any_slow(L), nsq = weights.norms_sq != nullptr;
+#define DPSGD_ANY(T_, M_, S_, Q_) \
+  launch_any<T_, M_, S_, Q_>(layers, idx, n, weights, outs, splits, accumulate, nullptr, nullptr, 0, stream)
+#define DPSGD_ANY_FLAT(T_)                                                                  \
+  (slow ? (nsq ? DPSGD_ANY(T_, ANY_FLAT, true, true) : DPSGD_ANY(T_, ANY_FLAT, true, false)) \
+        : (nsq ? DPSGD_ANY(T_, ANY_FLAT, false, true) : DPSGD_ANY(T_, ANY_FLAT, false, false)))
+  if (L.dtype == DPSGD_F32) return DPSGD_ANY_FLAT(float);
+  if (any_flat(L)) return DPSGD_ANY_FLAT(uint16_t);
+  return slow ? DPSGD_ANY(uint16_t, ANY_EX, true, false) : DPSGD_ANY(uint16_t, ANY_EX, false, false);
+#undef DPSGD_ANY_FLAT
 #undef DPSGD_ANY
 }
 
 int launch_any_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
                      float* partials, int64_t P, hipStream_t stream) {
   const dpsgd_layer& L = layers[idx[0]];
-  const bool narrow = any_shape(L) == 1, sh = any_slow(L);
-#define DPSGD_ANY(T_, S_)                                                                            \
-  (sh ? launch_any<T_, S_, ANY_SUMSQ, true>(layers, idx, n, nullptr, nullptr, nullptr, nullptr,     \
-                                            cols, partials, P, stream)                              \
-      : launch_any<T_, S_, ANY_SUMSQ, false>(layers, idx, n, nullptr, nullptr, nullptr, nullptr,    \
-                                             cols, partials, P, stream))
-  if (L.dtype == DPSGD_F32) return narrow ? DPSGD_ANY(float, 1) : DPSGD_ANY(float, 0);
-  return narrow ? DPSGD_ANY(uint16_t, 1) : DPSGD_ANY(uint16_t, 0);
+#define DPSGD_ANY(T_, S_)                                                                         \
+  launch_any<T_, ANY_SUMSQ, S_, false>(layers, idx, n, ClipWeights{}, nullptr, nullptr, nullptr, cols, \
+                                       partials, P, stream)
+  if (L.dtype == DPSGD_F32) return any_slow(L) ? DPSGD_ANY(float, true) : DPSGD_ANY(float, false);
+  return any_slow(L) ? DPSGD_ANY(uint16_t, true) : DPSGD_ANY(uint16_t, false);
 #undef DPSGD_ANY
 }
 
