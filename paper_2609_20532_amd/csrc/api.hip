@@ -125,15 +125,31 @@ NormPlan plan_norms(const dpsgd_layer* layers, int32_t n, int32_t mode, bool par
 
 constexpr size_t kFactorBytesAlign = 256;
 
-size_t clip_ws_bytes(const dpsgd_layer* layers, int32_t n) {
+// Plans the launches of a clipped sum; `plan` receives the last one's (the only
+// one's, for up to kMaxLayersPerLaunch layers).
+size_t clip_ws_bytes(const dpsgd_layer* layers, int32_t n, ClipPlan* plan) {
   size_t part = 0;
   for (int32_t base = 0; base < n; base += kMaxLayersPerLaunch) {
     const int m = n - base < kMaxLayersPerLaunch ? n - base : kMaxLayersPerLaunch;
-    ClipPlan plan;
-    plan_clip(layers + base, m, &plan);
-    if (plan.partial_bytes > part) part = plan.partial_bytes;
+    plan_clip(layers + base, m, plan);
+    if (plan->partial_bytes > part) part = plan->partial_bytes;
   }
   return round_up((size_t)layers[0].B * sizeof(float), kFactorBytesAlign) + part;
+}
+
+// Runs the clipped sums of n layers, up to kMaxLayersPerLaunch a launch; `plan`
+// is clip_ws_bytes'.
+int run_clip_sums(const dpsgd_layer* layers, int32_t n, const ClipWeights& weights,
+                  float* const* grads, int accumulate, float* partial_base, ClipPlan* plan,
+                  hipStream_t stream) {
+  for (int32_t base = 0; base < n; base += kMaxLayersPerLaunch) {
+    const int m = n - base < kMaxLayersPerLaunch ? n - base : kMaxLayersPerLaunch;
+    if (n > kMaxLayersPerLaunch) plan_clip(layers + base, m, plan);
+    const int st = launch_clip_sum(layers + base, m, weights, grads + base, accumulate, partial_base,
+                                   *plan, stream);
+    if (st != DPSGD_OK) return st;
+  }
+  return DPSGD_OK;
 }
 
 bool bad_float(float x) { return isnan(x); }
@@ -158,6 +174,7 @@ struct StepPlan {
   std::vector<size_t> store_off;        // per stored layer, from the store base
   std::vector<dpsgd_layer> other_layers;
   size_t clip_off = 0, store_base = 0, total = 0;
+  ClipPlan clip;
 };
 
 StepPlan plan_step(const dpsgd_layer* layers, int32_t n, int32_t mode) {
@@ -176,7 +193,7 @@ StepPlan plan_step(const dpsgd_layer* layers, int32_t n, int32_t mode) {
   for (int l : p.other) p.other_layers.push_back(layers[l]);
   const size_t clip = p.other.empty()
                           ? round_up((size_t)B * sizeof(float), kFactorBytesAlign)
-                          : clip_ws_bytes(p.other_layers.data(), (int32_t)p.other.size());
+                          : clip_ws_bytes(p.other_layers.data(), (int32_t)p.other.size(), &p.clip);
   p.splits.resize(p.stored.size());
   if (!p.stored.empty())
     plan_skinny(layers, p.stored.data(), (int)p.stored.size(), tr_cu_count(), p.splits.data());
@@ -310,7 +327,8 @@ int dpsgd_clip_factors(const float* norms_sq, int64_t B, float C, float* factors
 
 size_t dpsgd_clip_workspace_bytes(const dpsgd_layer* layers, int32_t n_layers) {
   if (check_layers(layers, n_layers, false) != DPSGD_OK) return 0;
-  return clip_ws_bytes(layers, n_layers);
+  ClipPlan plan;
+  return clip_ws_bytes(layers, n_layers, &plan);
 }
 
 int dpsgd_clip_accumulate_multi(const dpsgd_layer* layers, int32_t n_layers,
@@ -323,7 +341,8 @@ int dpsgd_clip_accumulate_multi(const dpsgd_layer* layers, int32_t n_layers,
   for (int32_t l = 0; l < n_layers; ++l)
     if (!grads[l] || !aligned16(grads[l])) return DPSGD_ERR_INVALID_ARG;
   if (bad_float(C) || !(C > 0.0f)) return DPSGD_ERR_INVALID_ARG;
-  const size_t need = clip_ws_bytes(layers, n_layers);
+  ClipPlan plan;
+  const size_t need = clip_ws_bytes(layers, n_layers, &plan);
   if (!workspace || workspace_bytes < need) return DPSGD_ERR_WORKSPACE;
   if (!aligned16(workspace)) return DPSGD_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -348,15 +367,7 @@ int dpsgd_clip_accumulate_multi(const dpsgd_layer* layers, int32_t n_layers,
     st = launch_clip_factors(norms_sq, B, C, factors, factors_out, mask_out, s);
     if (st != DPSGD_OK) return st;
   }
-  for (int32_t base = 0; base < n_layers; base += kMaxLayersPerLaunch) {
-    const int m = n_layers - base < kMaxLayersPerLaunch ? n_layers - base : kMaxLayersPerLaunch;
-    ClipPlan plan;
-    plan_clip(layers + base, m, &plan);
-    st = launch_clip_sum(layers + base, m, weights, grads + base, accumulate ? 1 : 0,
-                         partial_base, plan, s);
-    if (st != DPSGD_OK) return st;
-  }
-  return DPSGD_OK;
+  return run_clip_sums(layers, n_layers, weights, grads, accumulate ? 1 : 0, partial_base, &plan, s);
 }
 
 int dpsgd_clip_accumulate(const dpsgd_layer* layer, const float* norms_sq, float C, float* grad,
@@ -384,7 +395,7 @@ int dpsgd_clipped_sum_multi(const dpsgd_layer* layers, int32_t n_layers, int32_t
   for (int32_t l = 0; l < n_layers; ++l)
     if (!grads[l] || !aligned16(grads[l])) return DPSGD_ERR_INVALID_ARG;
   if (bad_float(C) || !(C > 0.0f)) return DPSGD_ERR_INVALID_ARG;
-  const StepPlan p = plan_step(layers, n_layers, mode);
+  StepPlan p = plan_step(layers, n_layers, mode);
   if (!workspace || workspace_bytes < p.total) return DPSGD_ERR_WORKSPACE;
   if (!aligned16(workspace)) return DPSGD_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -423,14 +434,9 @@ int dpsgd_clipped_sum_multi(const dpsgd_layer* layers, int32_t n_layers, int32_t
   const int n_ot = (int)p.other.size();
   std::vector<float*> other_grads;
   for (int l : p.other) other_grads.push_back(grads[l]);
-  for (int base = 0; base < n_ot; base += kMaxLayersPerLaunch) {
-    const int m = n_ot - base < kMaxLayersPerLaunch ? n_ot - base : kMaxLayersPerLaunch;
-    ClipPlan plan;
-    plan_clip(p.other_layers.data() + base, m, &plan);
-    st = launch_clip_sum(p.other_layers.data() + base, m, weights, other_grads.data() + base,
-                         accumulate ? 1 : 0, clip_partials, plan, s);
-    if (st != DPSGD_OK) return st;
-  }
+  st = run_clip_sums(p.other_layers.data(), n_ot, weights, other_grads.data(), accumulate ? 1 : 0,
+                     clip_partials, &p.clip, s);
+  if (st != DPSGD_OK) return st;
   if (n_st > 0)
     return launch_skinny_clip(layers, p.stored.data(), n_st, stores.data(), factors,
                               stored_grads.data(), accumulate ? 1 : 0, s);

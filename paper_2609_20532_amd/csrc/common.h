@@ -277,6 +277,7 @@ int launch_clip_factors(const float* norms_sq, int64_t B, float C, float* factor
 
 // Split plan of the clip-weighted sum.
 struct ClipPlan {
+  int8_t group[kMaxLayersPerLaunch];             // the launch that takes the layer (gemm.hip)
   int splits[kMaxLayersPerLaunch];
   size_t partial_offset[kMaxLayersPerLaunch];  // bytes from the partial base
   size_t partial_bytes;                          // total (split partials + 256-tile tail)
@@ -286,8 +287,6 @@ struct ClipPlan {
   size_t wide_offset;
   TrClipPlan ragged;                             // layers on its instance for any T and widths
   size_t ragged_offset;
-  bool use_ragged;                               // whether that instance is used at all
-  bool merge_shapes;                             // any-shape layers of both shapes share launches
 };
 void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan);
 

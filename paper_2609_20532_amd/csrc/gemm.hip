@@ -264,10 +264,21 @@ double clip_flops(const dpsgd_layer& L) {
   return 2.0 * (double)(L.B * L.T) * (double)L.d_in * (double)L.d_out;
 }
 
-// Whether the any-shape kernel takes the layer's clipped sum; ragged: the
-// launch sends its wide_ragged_ok layers to the 384x256 tiles.
-bool any_clip(const dpsgd_layer& L, bool ragged) {
-  return !wide_tile_ok(L) && !tr_tile_ok(L) && !(ragged && wide_ragged_ok(L)) && !tiny_clip_ok(L);
+// Launches of a clipped sum: the any-shape ones, then the other kernels'.
+enum ClipGroup : int {
+  kTr = kAnyGroups,
+  kWide = kAnyGroups + 1,
+  kTiny = kAnyGroups + 2,
+  kRagged = kAnyGroups + 3,   // 384x256 tiles with padding, if the launch uses them
+  kClipGroups = kAnyGroups + 4
+};
+// The group of a layer's clipped sum; any-shape layers get kAnyGroups' first.
+int clip_class(const dpsgd_layer& L) {
+  return wide_tile_ok(L)     ? kWide
+         : tr_tile_ok(L)     ? kTr
+         : wide_ragged_ok(L) ? kRagged
+         : tiny_clip_ok(L)   ? kTiny
+                             : 0;
 }
 
 }  // namespace
@@ -283,8 +294,6 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   // The balance is per launch (launches run one after the other, so each fills
   // the GPU on its own).
   const int cus = tr_cu_count();
-  int tr_idx[kMaxLayersPerLaunch], n_tr = 0, wd_idx[kMaxLayersPerLaunch], n_wd = 0;
-  int rg_idx[kMaxLayersPerLaunch], n_rg = 0;
   // The 384x256 tiles of the layers that they suit only with padding pay off
   // once the launch holds enough work for its prologues and partial tiles:
   // single layers of 8, 10, 12 and 13 GFLOP took 37.9, 38.9, 42.9 and 45.3 us
@@ -292,21 +301,21 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   // 33, 48 and 164 GFLOP 72.9, 64.1, 79.5 and 180 against 79.2, 72.7, 98.9 and
   // 300 us.
   constexpr double kMinRaggedFlops = 2.0e10;
-  double ragged_flops = 0.0;
-  for (int l = 0; l < n_layers; ++l)
-    if (wide_ragged_ok(layers[l])) ragged_flops += clip_flops(layers[l]);
-  plan->use_ragged = ragged_flops >= kMinRaggedFlops;
-  double any_flops = 0.0;
-  for (int l = 0; l < n_layers; ++l)
-    if (any_clip(layers[l], plan->use_ragged)) any_flops += clip_flops(layers[l]);
-  const bool merge = plan->merge_shapes = any_flops <= kMergeFlops;
-  int any_idx[kAnyGroups][kMaxLayersPerLaunch], n_any[kAnyGroups] = {};
+  double ragged_flops = 0.0, any_flops = 0.0;
   for (int l = 0; l < n_layers; ++l) {
-    const dpsgd_layer& L = layers[l];
-    if (wide_tile_ok(L)) wd_idx[n_wd++] = l;
-    else if (tr_tile_ok(L)) tr_idx[n_tr++] = l;
-    else if (plan->use_ragged && wide_ragged_ok(L)) rg_idx[n_rg++] = l;
-    else if (any_clip(L, plan->use_ragged)) any_idx[any_group(L, merge)][n_any[any_group(L, merge)]++] = l;
+    plan->group[l] = (int8_t)clip_class(layers[l]);
+    if (plan->group[l] == kRagged) ragged_flops += clip_flops(layers[l]);
+    if (plan->group[l] == 0) any_flops += clip_flops(layers[l]);
+  }
+  const bool ragged = ragged_flops >= kMinRaggedFlops;
+  if (!ragged) any_flops += ragged_flops;
+  const bool merge = any_flops <= kMergeFlops;
+  int idx[kClipGroups][kMaxLayersPerLaunch], cnt[kClipGroups] = {};
+  for (int l = 0; l < n_layers; ++l) {
+    int g = plan->group[l];
+    if (g == 0 || (g == kRagged && !ragged)) g = any_group(layers[l], merge);
+    plan->group[l] = (int8_t)g;
+    idx[g][cnt[g]++] = l;
   }
   constexpr int64_t kMinSlicesPerSplit = 4;
   constexpr int64_t kMaxSplits = 1024;
@@ -319,7 +328,7 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   int64_t chunk_of[kAnyGroups];
   for (int64_t& c : chunk_of) c = 1;
   for (int g = 0; g < kAnyGroups; ++g) {
-    if (n_any[g] == 0) continue;
+    if (cnt[g] == 0) continue;
     // A launch runs in rounds of as many workgroups as the GPU holds, and a
     // round that is only partly filled costs as much as a full one, so the
     // chunk (slices per workgroup) is chosen per launch: for r = 1 .. 8
@@ -327,20 +336,20 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
     // with the least estimated time: r x (longest workgroup) plus the partial
     // sums written and read back. The rates are what the kernel and the
     // reduction sustain (a slice at the kernel's rate on a full GPU).
-    const dpsgd_layer& L0 = layers[any_idx[g][0]];
+    const dpsgd_layer& L0 = layers[idx[g][0]];
     const int64_t slots = (int64_t)any_workgroups_per_cu() * cus;
     const double rate = L0.dtype == DPSGD_F32 ? 1.4e14 : 6.0e14;
     const double t_slice = 2.0 * 128 * 128 * any_slice_rows(L0) * (double)slots / rate;
     constexpr double kHbm = 4.0e12;
     int64_t q_max = 1;
-    for (int k = 0; k < n_any[g]; ++k) q_max = std::max(q_max, any_slices(layers[any_idx[g][k]]));
+    for (int k = 0; k < cnt[g]; ++k) q_max = std::max(q_max, any_slices(layers[idx[g][k]]));
     // Workgroups of the launch for a given chunk, its longest K range and the
     // bytes of its partial sums.
     auto eval = [&](int64_t chunk, int64_t* longest, double* bytes) {
       int64_t wgs = 0, lg = 0;
       double by = 0.0;
-      for (int k = 0; k < n_any[g]; ++k) {
-        const dpsgd_layer& L = layers[any_idx[g][k]];
+      for (int k = 0; k < cnt[g]; ++k) {
+        const dpsgd_layer& L = layers[idx[g][k]];
         const int64_t q = any_slices(L);
         const int64_t sp = split_count(q, chunk);
         wgs += any_tiles(L) * sp;
@@ -372,17 +381,18 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
     int64_t s = 1;
-    if (any_clip(L, plan->use_ragged)) s = split_count(any_slices(L), chunk_of[any_group(L, merge)]);
-    else if (tiny_clip_ok(L)) s = tiny_jobs(L);   // one partial per job of consecutive examples
+    const int g = plan->group[l];
+    if (g < kAnyGroups) s = split_count(any_slices(L), chunk_of[g]);
+    else if (g == kTiny) s = tiny_jobs(L);   // one partial per job of consecutive examples
     plan->splits[l] = (int)s;
     plan->partial_offset[l] = off;
     if (s > 1) off += round_up((size_t)s * (size_t)L.d_out * (size_t)L.d_in * sizeof(float), 256);
   }
-  plan_tr_clip(layers, tr_idx, n_tr, cus, &plan->tr);
-  plan_wide_clip(layers, wd_idx, n_wd, cus, &plan->wide);
+  plan_tr_clip(layers, idx[kTr], cnt[kTr], cus, &plan->tr);
+  plan_wide_clip(layers, idx[kWide], cnt[kWide], cus, &plan->wide);
   plan->tr_offset = off;
   plan->wide_offset = off + round_up(plan->tr.tail_bytes, 256);
-  plan_wide_clip(layers, rg_idx, n_rg, cus, &plan->ragged);
+  plan_wide_clip(layers, idx[kRagged], cnt[kRagged], cus, &plan->ragged);
   plan->ragged_offset = plan->wide_offset + round_up(plan->wide.tail_bytes, 256);
   plan->partial_bytes = plan->ragged_offset + round_up(plan->ragged.tail_bytes, 256);
 }
@@ -395,7 +405,7 @@ bool clip_from_norms(const dpsgd_layer* layers, int n_layers) {
   double flops = 0.0;
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
-    if (!any_clip(L, true) || any_group(L, true) != any_group(layers[0], true) || !any_flat(L)) return false;
+    if (clip_class(L) != 0 || any_group(L, true) != any_group(layers[0], true) || !any_flat(L)) return false;
     flops += clip_flops(L);
   }
   return n_layers <= kMaxLayersPerLaunch && flops <= kMostFlops;
@@ -405,20 +415,13 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const ClipWeights& 
                     float* const* grads, int accumulate, float* partial_base, const ClipPlan& plan,
                     hipStream_t stream) {
   // Group layers by kernel variant; each group is one grouped launch.
-  constexpr int kTr = kAnyGroups, kWide = kAnyGroups + 1, kTiny = kAnyGroups + 2,
-                kRagged = kAnyGroups + 3, kClipGroups = kAnyGroups + 4;
   int idx[kClipGroups][kMaxLayersPerLaunch];
   float* outs[kClipGroups][kMaxLayersPerLaunch];
   int spl[kClipGroups][kMaxLayersPerLaunch];
   int acc[kClipGroups][kMaxLayersPerLaunch];
   int cnt[kClipGroups] = {};
   for (int l = 0; l < n_layers; ++l) {
-    const dpsgd_layer& L = layers[l];
-    const int g = wide_tile_ok(L)     ? kWide
-                  : tr_tile_ok(L)     ? kTr
-                  : plan.use_ragged && wide_ragged_ok(L) ? kRagged
-                  : tiny_clip_ok(L) ? kTiny
-                                    : any_group(L, plan.merge_shapes);
+    const int g = plan.group[l];
     const int k = cnt[g]++;
     idx[g][k] = l;
     spl[g][k] = plan.splits[l];

@@ -26,6 +26,8 @@
 // kept in units of the current example's factor and multiplied by
 // c_prev / c_next at each example boundary
 // (paper: Section 2.2, g_bar_i = c_i g_i summed over the batch).
+#include <atomic>
+
 #include "lds_dma.h"
 #include "mma.h"
 
@@ -409,14 +411,20 @@ bool tr_tile_ok(const dpsgd_layer& L) {
 int64_t tr_q_total(const dpsgd_layer& L) { return L.B * (L.T / kTrBK); }
 
 int tr_cu_count() {
+  // The planners ask several times per layer: one runtime query per device.
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];
   int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus <= 0) {
-    (void)hipGetLastError();
-    return 256;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kDevices) {
+    cus = known[dev].load(std::memory_order_relaxed);
+    if (cus > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
+      known[dev].store(cus, std::memory_order_relaxed);
+      return cus;
+    }
   }
-  return cus;
+  (void)hipGetLastError();
+  return 256;
 }
 
 void plan_tr_clip(const dpsgd_layer* layers, const int* idx, int n, int cus, TrClipPlan* plan) {

@@ -434,12 +434,12 @@ bool wide_tile_ok(const dpsgd_layer& L) {
   // split along K, and the 256 x 256 kernel, whose tiles fill the round, was
   // faster (4096 x 4096, B T = 16384: 0.53 against 0.66 ms), while with
   // several rounds the 384-row tile wins (11008 x 4096: 1.30 against 1.35 ms).
+  if (L.dtype != DPSGD_BF16 || L.d_in % kWdTN != 0 || L.T % kWdBK != 0 || L.d_out % 32 != 0 ||
+      L.d_in > (INT64_C(1) << 24) || L.d_out > (INT64_C(1) << 24))
+    return false;
+  if (L.d_out % kWdTM == 0) return true;
   const int64_t tm = wide_tiles_m(L), pad = tm * kWdTM - L.d_out;
-  const bool whole = L.d_out % kWdTM == 0;
-  const bool ragged = L.d_out % 32 == 0 && 50 * pad <= 3 * L.d_out &&
-                      tm * (L.d_in / kWdTN) >= tr_cu_count();
-  return L.dtype == DPSGD_BF16 && (whole || ragged) && L.d_in % kWdTN == 0 && L.T % kWdBK == 0 &&
-         L.d_in <= (INT64_C(1) << 24) && L.d_out <= (INT64_C(1) << 24);
+  return 50 * pad <= 3 * L.d_out && tm * (L.d_in / kWdTN) >= tr_cu_count();
 }
 
 bool wide_ragged_ok(const dpsgd_layer& L) {
