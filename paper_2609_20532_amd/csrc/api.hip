@@ -420,7 +420,14 @@ int dpsgd_clipped_sum_multi(const dpsgd_layer* layers, int32_t n_layers, int32_t
     if (st != DPSGD_OK) return st;
   }
   if (n_st > 0) {
-    st = launch_skinny_norms(layers, p.stored.data(), n_st, p.norms.cols.data(), p.splits.data(),
+    std::vector<const void*> read;
+    for (int32_t l = 0; l < n_layers; ++l) {
+      read.push_back(layers[l].A);
+      read.push_back(layers[l].G);
+    }
+    std::sort(read.begin(), read.end());
+    const bool shared = std::adjacent_find(read.begin(), read.end()) != read.end();
+    st = launch_skinny_norms(layers, p.stored.data(), n_st, shared, p.norms.cols.data(), p.splits.data(),
                              stores.data(), partials, p.norms.P, s);
     if (st != DPSGD_OK) return st;
   }

@@ -138,8 +138,8 @@ bool skinny_ok(const dpsgd_layer& L);
 int64_t skinny_chunks(const dpsgd_layer& L);
 void plan_skinny(const dpsgd_layer* layers, const int* idx, int n, int cus, int64_t* splits);
 size_t skinny_store_bytes(const dpsgd_layer& L, int64_t splits);
-int launch_skinny_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
-                        const int64_t* splits, float* const* stores, float* partials, int64_t P,
+int launch_skinny_norms(const dpsgd_layer* layers, const int* idx, int n, bool shared,
+                        const int64_t* cols, const int64_t* splits, float* const* stores, float* partials, int64_t P,
                         hipStream_t stream);
 int launch_skinny_clip(const dpsgd_layer* layers, const int* idx, int n, float* const* stores,
                        const float* factors, float* const* outs, int accumulate,

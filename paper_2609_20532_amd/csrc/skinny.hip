@@ -74,6 +74,19 @@ struct SkVec<uint16_t, 4> {
   }
 };
 
+// A load of the wide side. STREAM: no other layer of the call reads the tensor,
+// so the lines need not stay in the caches: 24 float32 matrices of rank 4 (1.2
+// GB) 242 -> 226 us a call. Where layers share their activations plain loads let
+// the second find them in the cache. (The MFMA kernel below, whose loads cover
+// 256 bytes of a row, is slower with streaming loads: 48 bf16 matrices of rank
+// 8, d = 768: 165 us plain, 182 us streaming.)
+template <typename Raw, bool STREAM>
+__device__ __forceinline__ Raw sk_wide_load(const void* p) {
+  typedef uint32_t vec __attribute__((ext_vector_type(sizeof(Raw) / 4)));
+  const vec* v = static_cast<const vec*>(p);
+  return __builtin_bit_cast(Raw, STREAM ? __builtin_nontemporal_load(v) : *v);
+}
+
 __device__ __forceinline__ float sk_load(const float* p) { return *p; }
 __device__ __forceinline__ float sk_load(const uint16_t* p) { return bf16_to_f32(*p); }
 
@@ -88,7 +101,7 @@ __device__ __forceinline__ int sk_find_layer(const SkArgs& args, uint32_t job) {
 
 // Job w of a layer: chunk w % chunks, example (w / chunks) % B, row range
 // w / (chunks B).
-template <typename TIn, int R, int V>
+template <typename TIn, int R, int V, bool STREAM>
 __global__ __launch_bounds__(kThreads) void skinny_grad_kernel(SkArgs args) {
   typedef typename SkVec<TIn, V>::raw Raw;
   constexpr int G = 64 / R;   // rows per narrow load
@@ -136,7 +149,8 @@ __global__ __launch_bounds__(kThreads) void skinny_grad_kernel(SkArgs args) {
 #pragma unroll
     for (int u = 0; u < RI; ++u) {
       wv[u] = Raw{};
-      if (u < rows && col_ok) wv[u] = *reinterpret_cast<const Raw*>(W + (int64_t)(tg + u) * d_w);
+      if (u < rows && col_ok)
+        wv[u] = sk_wide_load<Raw, STREAM>(W + (int64_t)(tg + u) * d_w);
     }
 #pragma unroll
     for (int u = 0; u < RI; ++u) {
@@ -214,14 +228,31 @@ __device__ __forceinline__ bf16x8_t skm_bits(uint32_t w0, uint32_t w1, uint32_t 
   return __builtin_bit_cast(bf16x8_t, (u32x4_t{w0, w1, w2, w3}));
 }
 
-__global__ __launch_bounds__(kThreads) void skinny_mfma_kernel(SkArgs args) {
+// Loads are addressed by a scalar base and one 32-bit lane offset, without
+// branches: with per-row bounds checks and 64-bit lane addresses the kernel
+// spent 290 vector instructions per 32 rows (43 % of its time), and the narrow
+// side alone took eight 2-byte loads. QUADS (r a multiple of 4): the narrow
+// block of 32 rows is one contiguous run, loaded 8 bytes a lane, passed through
+// LDS and read back transposed (ds_read_b64_tr_b16). 48 matrices of rank 8,
+// d = 768, B = 48, T = 203 (547 MB): 119 -> 115 us,
+// bound by its reads; rank 16, d = 4096, B = 16, T = 1024 (268 MB): 70 -> 57 us.
+template <bool QUADS>
+__global__ __launch_bounds__(kThreads, 3) void skinny_mfma_kernel(SkArgs args) {
+  // QUADS: a wave's narrow block (1 KB at most) and 8 zero bytes for the
+  // columns past r.
+  __shared__ __attribute__((aligned(16))) char nlds[kSkWaves * 1024 + 16];
   // Scalar wave index and descriptor fields in registers, as in
   // skinny_grad_kernel.
-  const uint32_t job = blockIdx.x * kSkWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t job = blockIdx.x * kSkWaves + wave;
+  if (QUADS) {
+    if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(nlds + kSkWaves * 1024)[threadIdx.x] = 0u;
+    __syncthreads();
+  }
   if (job >= args.jobs) return;   // whole waves
   const int lane = threadIdx.x & 63;
   const SkEntry& E = args.L[sk_find_layer(args, job)];
-  const int64_t d_w = E.d_w, r = E.r;
+  const int d_w = E.d_w, r = E.r;
   const int T = E.T;
   const uint32_t w = job - E.job_begin;
   const int chunk = (int)(w % (uint32_t)E.chunks);
@@ -233,30 +264,66 @@ __global__ __launch_bounds__(kThreads) void skinny_mfma_kernel(SkArgs args) {
   const int g = lane >> 4, cl = lane & 15;
   const int col = chunk * kSkmCols + 8 * cl;
   const bool col_ok = col < d_w;   // d_w % 8 == 0: all eight columns or none
-  const uint16_t* W = static_cast<const uint16_t*>(E.wide) + i * T * d_w + (col_ok ? col : 0);
-  const uint16_t* Nr = static_cast<const uint16_t*>(E.narrow) + i * T * r;
+  // Row t of the example is row i T + t of the tensor; `ahead` rows remain from
+  // row t0 on (loads past them are clamped into the tensor and then cleared).
+  const uint32_t stride = 2u * (uint32_t)d_w, nstride = 2u * (uint32_t)r;
+  const char* Wb = static_cast<const char*>(E.wide) + (i * T + t0) * (int64_t)stride;
+  const char* Nb = static_cast<const char*>(E.narrow) + (i * T + t0) * (int64_t)nstride;
+  const int64_t ahead64 = ((int64_t)args.B - i) * T - t0;
+  const int ahead = (int)(ahead64 < 0x3FFFFFFF ? ahead64 : 0x3FFFFFFF);
+  const uint32_t woff = 8u * g * stride + 2u * (uint32_t)(col_ok ? col : 0);
   const bool n_ok = cl < r;
+  char* const nbuf = nlds + wave * 1024;
+  // Transposed reads of the narrow block: rows 8 g + 4 h + (l % 16) / 4, columns
+  // 4 (l % 4) .. +3.
+  const char* nrd[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = 8 * g + 4 * h + (cl >> 2), c4 = cl & 3;
+    nrd[h] = 4 * c4 < r ? nbuf + row * (int)nstride + 8 * c4 : nlds + kSkWaves * 1024;
+  }
 
   f32x4_t acc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   uint4 wv[8];
-  uint32_t nv[8];
-  auto load = [&](int tg) {
+  uint32_t nv[8];   // !QUADS
+  uint2 nq[2];      // QUADS
+  auto load = [&](int tr) {   // rows t0 + tr .. + 31
+    // Row bases and offsets stay inside the tensor: the lanes of load kk reach
+    // 24 rows and one row's bytes further.
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-      const int t = tg + 8 * g + kk;
-      wv[kk] = uint4{0u, 0u, 0u, 0u};
-      nv[kk] = 0u;
-      if (t < t1) {
-        if (col_ok) wv[kk] = *reinterpret_cast<const uint4*>(W + (int64_t)t * d_w);
-        if (n_ok) nv[kk] = Nr[(int64_t)t * r + cl];
+      const int row = min(tr + kk, ahead - 1);
+      const uint32_t end = (uint32_t)min(ahead - row, 25) * stride - 16u;
+      wv[kk] = *reinterpret_cast<const uint4*>(Wb + (uint64_t)(uint32_t)row * stride + min(woff, end));
+    }
+    const int nrow = min(tr, ahead - 1), left = ahead - nrow;
+    if (QUADS) {
+      // 8-byte chunk c of the run of 32 rows: 8 r chunks.
+      const uint64_t base = (uint64_t)(uint32_t)nrow * nstride;
+      const uint32_t last = (uint32_t)min(left, 32) * (uint32_t)(r >> 2) - 1u;
+      __builtin_memcpy(&nq[0], Nb + base + 8u * min((uint32_t)lane, last), 8);
+      __builtin_memcpy(&nq[1], Nb + base + 8u * min(64u + (uint32_t)lane, last), 8);
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const int row = min(8 * g + kk, left - 1);
+        nv[kk] = *reinterpret_cast<const uint16_t*>(
+            Nb + (uint64_t)(uint32_t)nrow * nstride + (uint32_t)row * nstride + (n_ok ? 2u * cl : 0u));
       }
     }
   };
-  if (t0 < t1) load(t0);
-  for (int tg = t0; tg < t1; tg += 32) {
+  const int nr = t1 - t0;
+  load(0);
+  for (int tr = 0; tr < nr; tr += 32) {
+    const int rows = nr - tr;   // valid rows of this block
+    if (rows < 32 || !col_ok) {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        if (8 * g + kk >= rows || !col_ok) wv[kk] = make_uint4(0u, 0u, 0u, 0u);
+    }
     // Transpose the 8 x 8 block: word q of operand j packs rows 2q and
     // 2q + 1 of column j (the low halves of word j / 2 for even j, the high
     // halves for odd j).
@@ -273,9 +340,30 @@ __global__ __launch_bounds__(kThreads) void skinny_mfma_kernel(SkArgs args) {
       c[6][q] = __builtin_amdgcn_perm(y.w, x.w, 0x05040100u);
       c[7][q] = __builtin_amdgcn_perm(y.w, x.w, 0x07060302u);
     }
-    const bf16x8_t a = skm_bits(nv[0] | (nv[1] << 16), nv[2] | (nv[3] << 16),
-                                nv[4] | (nv[5] << 16), nv[6] | (nv[7] << 16));
-    if (tg + 32 < t1) load(tg + 32);
+    bf16x8_t a;
+    if (QUADS) {
+      if (rows < 32) {
+        const uint32_t valid = (uint32_t)rows * (uint32_t)(r >> 2);
+        if ((uint32_t)lane >= valid) nq[0] = make_uint2(0u, 0u);
+        if (64u + (uint32_t)lane >= valid) nq[1] = make_uint2(0u, 0u);
+      }
+      if (lane < 8 * r) *reinterpret_cast<uint2*>(nbuf + 8 * lane) = nq[0];
+      if (64 + lane < 8 * r) *reinterpret_cast<uint2*>(nbuf + 512 + 8 * lane) = nq[1];
+      typedef short v4i16_t __attribute__((ext_vector_type(4)));
+      typedef short v8i16_t __attribute__((ext_vector_type(8)));
+      typedef __attribute__((address_space(3))) v4i16_t lds_v4i16;
+      const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)nrd[0]);
+      const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)nrd[1]);
+      const v8i16_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      a = __builtin_bit_cast(bf16x8_t, v);
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        if (!n_ok || 8 * g + kk >= rows) nv[kk] = 0u;
+      a = skm_bits(nv[0] | (nv[1] << 16), nv[2] | (nv[3] << 16), nv[4] | (nv[5] << 16),
+                   nv[6] | (nv[7] << 16));
+    }
+    load(tr + 32);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
@@ -398,17 +486,24 @@ __global__ __launch_bounds__(kThreads) void skinny_clip_kernel(SkClipArgs args) 
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
   if (cnt == 4 && (E.n & 3) == 0) {
     // Whole groups of a layer with n % 4 == 0: 16-byte loads (every example's
-    // gradient starts 16-byte aligned), four examples in flight.
-#pragma unroll 4
-    for (int i = wave; i < args.B; i += kSkWaves) {
-      const float c = args.factors[i];
-      const float4 g = *reinterpret_cast<const float4*>(E.store + (int64_t)i * E.n + e0);
-      if (c != 0.0f) {
-        sum[0] = fmaf(c, g.x, sum[0]);
-        sum[1] = fmaf(c, g.y, sum[1]);
-        sum[2] = fmaf(c, g.z, sum[2]);
-        sum[3] = fmaf(c, g.w, sum[3]);
+    // gradient starts 16-byte aligned), kU examples in flight.
+    constexpr int kU = 12;
+    for (int i0 = wave; i0 < args.B; i0 += kU * kSkWaves) {
+      float c[kU];
+      f32x4_t g[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        // (Past the last example: the last one again, with weight 0.)
+        const int i = min(i0 + u * kSkWaves, args.B - 1);
+        c[u] = args.factors[i];
+        g[u] = *reinterpret_cast<const f32x4_t*>(E.store + (int64_t)i * E.n + e0);
       }
+#pragma unroll
+      for (int u = 0; u < kU; ++u)
+        if (i0 + u * kSkWaves < args.B && c[u] != 0.0f) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) sum[q] = fmaf(c[u], g[u][q], sum[q]);
+        }
     }
   } else if (cnt > 0) {
     for (int i = wave; i < args.B; i += kSkWaves) {
@@ -452,9 +547,12 @@ double sk_input_bytes(const dpsgd_layer& L) {
 }
 
 template <typename TIn, int R, int V>
-void launch_grad(const SkArgs& args, hipStream_t stream) {
+void launch_grad(const SkArgs& args, bool once, hipStream_t stream) {
   const uint32_t wgs = (args.jobs + kSkWaves - 1) / kSkWaves;
-  hipLaunchKernelGGL((skinny_grad_kernel<TIn, R, V>), dim3(wgs), dim3(kThreads), 0, stream, args);
+  if (once)
+    hipLaunchKernelGGL((skinny_grad_kernel<TIn, R, V, true>), dim3(wgs), dim3(kThreads), 0, stream, args);
+  else
+    hipLaunchKernelGGL((skinny_grad_kernel<TIn, R, V, false>), dim3(wgs), dim3(kThreads), 0, stream, args);
 }
 
 }  // namespace
@@ -467,8 +565,11 @@ bool skinny_ok(const dpsgd_layer& L) {
   return 4.0 * sk_grad_bytes(L) <= sk_input_bytes(L);
 }
 
-// bf16 layers whose wide side is a multiple of 8 take the MFMA kernel.
-bool sk_mfma(const dpsgd_layer& L) { return L.dtype == DPSGD_BF16 && sk_wide(L) % 8 == 0; }
+// bf16 layers whose wide side is a multiple of 8 take the MFMA kernel (whose
+// lane offsets reach 32 rows in 32 bits).
+bool sk_mfma(const dpsgd_layer& L) {
+  return L.dtype == DPSGD_BF16 && sk_wide(L) % 8 == 0 && sk_wide(L) <= (INT64_C(1) << 25);
+}
 
 int64_t skinny_chunks(const dpsgd_layer& L) {
   return ceil_div(sk_wide(L), sk_mfma(L) ? kSkmCols : 64 * sk_vec(L));
@@ -496,15 +597,16 @@ size_t skinny_store_bytes(const dpsgd_layer& L, int64_t splits) {
 }
 
 // One pair of launches (grad, then finish when a layer has several row
-// ranges) per class and per kMaxLayersPerLaunch layers: the MFMA class
-// (class 0), then the VALU kernel's classes of padded rank R, which fix its R
-// and V.
-int launch_skinny_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
-                        const int64_t* splits, float* const* stores, float* partials, int64_t P,
+// ranges) per class and per kMaxLayersPerLaunch layers: the MFMA classes
+// (class 0 for ranks that are multiples of 4, 1 for others), then the VALU
+// kernel's classes of padded rank R, which fix its R and V.
+// shared: some tensor of the call is read by more than one layer.
+int launch_skinny_norms(const dpsgd_layer* layers, const int* idx, int n, bool shared,
+                        const int64_t* cols, const int64_t* splits, float* const* stores, float* partials, int64_t P,
                         hipStream_t stream) {
   if (n <= 0) return DPSGD_OK;
-  const bool bf16 = layers[idx[0]].dtype == DPSGD_BF16;
-  for (int R : {0, 4, 8, 16}) {
+  const bool bf16 = layers[idx[0]].dtype == DPSGD_BF16, once = !shared;
+  for (int R : {0, 1, 4, 8, 16}) {
     int pos[kMaxLayersPerLaunch];
     int k0 = 0;
     while (k0 < n) {
@@ -512,7 +614,7 @@ int launch_skinny_norms(const dpsgd_layer* layers, const int* idx, int n, const 
       int m = 0;
       for (; k0 < n && m < kMaxLayersPerLaunch; ++k0) {
         const dpsgd_layer& L = layers[idx[k0]];
-        if ((sk_mfma(L) ? 0 : sk_rpad(L)) == R) pos[m++] = k0;
+        if ((sk_mfma(L) ? (sk_rank(L) % 4 == 0 ? 0 : 1) : sk_rpad(L)) == R) pos[m++] = k0;
       }
       if (m == 0) break;
       SkArgs ga{}, fa{};
@@ -547,22 +649,24 @@ int launch_skinny_norms(const dpsgd_layer* layers, const int* idx, int n, const 
       if (gjobs > 0x7FFFFFFF || fjobs > 0x7FFFFFFF) return DPSGD_ERR_INVALID_ARG;
       ga.jobs = (uint32_t)gjobs;
       fa.jobs = (uint32_t)fjobs;
+      const dim3 mfma_wgs((ga.jobs + kSkWaves - 1) / kSkWaves);
       if (R == 0) {
-        hipLaunchKernelGGL(skinny_mfma_kernel, dim3((ga.jobs + kSkWaves - 1) / kSkWaves),
-                           dim3(kThreads), 0, stream, ga);
+        hipLaunchKernelGGL(skinny_mfma_kernel<true>, mfma_wgs, dim3(kThreads), 0, stream, ga);
+      } else if (R == 1) {
+        hipLaunchKernelGGL(skinny_mfma_kernel<false>, mfma_wgs, dim3(kThreads), 0, stream, ga);
       } else if (bf16) {
-        if (R == 4) launch_grad<uint16_t, 4, 4>(ga, stream);
-        else if (R == 8) launch_grad<uint16_t, 8, 4>(ga, stream);
-        else launch_grad<uint16_t, 16, 4>(ga, stream);
+        if (R == 4) launch_grad<uint16_t, 4, 4>(ga, once, stream);
+        else if (R == 8) launch_grad<uint16_t, 8, 4>(ga, once, stream);
+        else launch_grad<uint16_t, 16, 4>(ga, once, stream);
       } else {
-        if (R == 4) launch_grad<float, 4, 4>(ga, stream);
-        else if (R == 8) launch_grad<float, 8, 4>(ga, stream);
-        else launch_grad<float, 16, 4>(ga, stream);
+        if (R == 4) launch_grad<float, 4, 4>(ga, once, stream);
+        else if (R == 8) launch_grad<float, 8, 4>(ga, once, stream);
+        else launch_grad<float, 16, 4>(ga, once, stream);
       }
       if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
       if (fjobs > 0) {
         // Chunks of 64 V wide columns: 128 for the MFMA class, 256 otherwise.
-        if (R == 0)
+        if (R <= 1)
           hipLaunchKernelGGL(skinny_finish_kernel<kSkmCols / 64>, dim3(fa.jobs), dim3(kThreads), 0,
                              stream, fa);
         else
