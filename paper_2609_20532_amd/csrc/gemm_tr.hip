@@ -332,12 +332,15 @@ __global__ __launch_bounds__(kTrThreads, 1) void tgemm_tr_kernel(TrArgs args) {
   // gradient. Tail worker p = job - n_full owns range p % tail_w of tail tile
   // p / tail_w and stores a partial tile.
   const bool whole = job < args.n_full;
-  uint32_t tile_g = job, qa = 0, qb = 0;
+  uint32_t tile_g = job, part = 0, qa = 0, qb = 0;
   if (!whole) {
+    // Range-major, as in gemm_wide.hip.
     const uint32_t p = job - args.n_full, w = (uint32_t)args.tail_w;
-    tile_g = args.n_full + p / w;
-    qa = tail_range_begin(p % w, (uint32_t)args.Q, w);
-    qb = tail_range_begin(p % w + 1, (uint32_t)args.Q, w);
+    const uint32_t n_tail_tiles = args.n_tiles - args.n_full, k = p / n_tail_tiles;
+    tile_g = args.n_full + p % n_tail_tiles;
+    part = (p % n_tail_tiles) * w + k;
+    qa = tail_range_begin(k, (uint32_t)args.Q, w);
+    qb = tail_range_begin(k + 1, (uint32_t)args.Q, w);
   }
   const int l = find_layer(args, tile_g);
   const TrEntry& E = args.L[l];
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(kTrThreads, 1) void tgemm_tr_kernel(TrArgs args) {
                            : tr_segment<true, false>(E, tm, tn, qa, q_end, args.factors, lds, ln, acc);
   // One store for both cases (two inlined copies raise register pressure).
   float* dst = whole ? E.out + (int64_t)tm * kTrTile * E.N + tn * kTrTile
-                     : args.partials + (int64_t)(job - args.n_full) * kTrTile * kTrTile;
+                     : args.partials + (int64_t)part * kTrTile * kTrTile;
   const int64_t ld = whole ? (int64_t)E.N : (int64_t)kTrTile;
   store_tile(dst, ld, acc, c, whole && args.accumulate);
 }

@@ -356,12 +356,16 @@ __global__ __launch_bounds__(kWdThreads, 1) void tgemm_wide_kernel(WdArgs args) 
   WdAcc acc;
   const uint32_t job = xcd_two_class_index(blockIdx.x, gridDim.x, args.n_full);
   const bool whole = job < args.n_full;
-  uint32_t tile_g = job, qa = 0, qb = 0;
+  uint32_t tile_g = job, part = 0, qa = 0, qb = 0;
   if (!whole) {
+    // Range-major: neighbouring jobs (one XCD) take neighbouring tiles of one K
+    // range, which read the same rows of G and A.
     const uint32_t p = job - args.n_full, w = (uint32_t)args.tail_w;
-    tile_g = args.n_full + p / w;
-    qa = wd_range_begin(p % w, (uint32_t)args.Q, w);
-    qb = wd_range_begin(p % w + 1, (uint32_t)args.Q, w);
+    const uint32_t n_tail_tiles = args.n_tiles - args.n_full, k = p / n_tail_tiles;
+    tile_g = args.n_full + p % n_tail_tiles;
+    part = (p % n_tail_tiles) * w + k;
+    qa = wd_range_begin(k, (uint32_t)args.Q, w);
+    qb = wd_range_begin(k + 1, (uint32_t)args.Q, w);
   }
   const int l = wd_find_layer(args, tile_g);
   const WdEntry& E = args.L[l];
@@ -386,7 +390,7 @@ __global__ __launch_bounds__(kWdThreads, 1) void tgemm_wide_kernel(WdArgs args) 
       any_zero ? wd_segment<true, RAGGED>(E, tm, tn, qa, q_end, args.factors, lds, acc)
                : wd_segment<false, RAGGED>(E, tm, tn, qa, q_end, args.factors, lds, acc);
   float* dst = whole ? E.out + (int64_t)tm * kWdTM * E.N + tn * kWdTN
-                     : args.partials + (int64_t)(job - args.n_full) * kWdTileElems;
+                     : args.partials + (int64_t)part * kWdTileElems;
   const int64_t ld = whole ? (int64_t)E.N : (int64_t)kWdTN;
   wd_store(dst, ld, acc, c, whole && args.accumulate, min(kWdTM, E.M - tm * kWdTM),
            min(kWdTN, E.N - tn * kWdTN));
