@@ -135,25 +135,6 @@ __device__ __forceinline__ bf16x8_t any_frag(const char* p) {
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
-// 16 bytes shifted down by n elements of ES bytes (n >= 0); zeros come in.
-template <int ES>
-__device__ __forceinline__ uint4 any_shift(uint4 v, int n) {
-  const int bits = 8 * ES * n;
-  const uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
-  uint64_t a, b;
-  if (bits == 0) {
-    a = lo;
-    b = hi;
-  } else if (bits < 64) {
-    a = lo >> bits | hi << (64 - bits);
-    b = hi >> bits;
-  } else {
-    a = bits < 128 ? hi >> (bits - 64) : 0;
-    b = 0;
-  }
-  return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
-}
-
 // The wave's block over global rows [r0, r1), by float32 MFMAs with both
 // operands straight from memory (lane l: column l % 32 of a block, row l / 32
 // of two): for results that are not finite.
@@ -369,12 +350,12 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
     if (g_edge && (!SLOW || M >= C::kE)) {
 #pragma unroll
       for (int u = 0; u < C::kLoadsM; ++u)
-        S.r[u] = any_shift<ES>(S.r[u], max(0, gcol + kColStep * (u / C::kWaveGroups) + C::kE - M));
+        S.r[u] = shift_chunk<ES>(S.r[u], max(0, gcol + kColStep * (u / C::kWaveGroups) + C::kE - M));
     }
     if (a_edge && (!SLOW || N >= C::kE)) {
 #pragma unroll
       for (int u = C::kLoadsM; u < C::kLoads; ++u)
-        S.r[u] = any_shift<ES>(
+        S.r[u] = shift_chunk<ES>(
             S.r[u], max(0, acol + kColStep * ((u - C::kLoadsM) / C::kWaveGroups) + C::kE - N));
     }
     // Rows that do not exist or whose clip factor is 0.

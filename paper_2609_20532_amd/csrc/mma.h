@@ -129,6 +129,25 @@ __device__ __forceinline__ uint32_t xcd_two_class_index(uint32_t bid, uint32_t n
   return n_first + (begin - f_begin) + (idx - f_cnt);
 }
 
+// 16 bytes shifted down by n elements of ES bytes (n >= 0); zeros come in.
+template <int ES>
+__device__ __forceinline__ uint4 shift_chunk(uint4 v, int n) {
+  const int bits = 8 * ES * n;
+  const uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
+  uint64_t a, b;
+  if (bits == 0) {
+    a = lo;
+    b = hi;
+  } else if (bits < 64) {
+    a = lo >> bits | hi << (64 - bits);
+    b = hi >> bits;
+  } else {
+    a = bits < 128 ? hi >> (bits - 64) : 0;
+    b = 0;
+  }
+  return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
+}
+
 // Element loads for the non-vector paths.
 __device__ __forceinline__ float load_elem(const uint16_t* p) { return bf16_to_f32(*p); }
 __device__ __forceinline__ float load_elem(const float* p) { return *p; }

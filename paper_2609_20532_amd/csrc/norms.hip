@@ -73,46 +73,57 @@ struct GhostArgs {
   float* partials;
 };
 
-// Raw 16-byte chunk c of a 128-row x BK tile of a row-major [rows][ld] matrix.
-template <typename TIn, bool VEC>
-__device__ __forceinline__ uint4 load_chunk(const TIn* X, int64_t ld, int row, int rows_valid,
-                                            int k, int d) {
-  constexpr int E = TileCfg<TIn>::E;
-  uint4 v = make_uint4(0u, 0u, 0u, 0u);
-  if (row >= rows_valid) return v;
-  const TIn* p = X + (int64_t)row * ld + k;
-  if (VEC) {
-    if (k < d) v = *reinterpret_cast<const uint4*>(p);
-  } else if (k + E <= d) {
-    // Rows of other widths start at any element: one 16-byte load without an
-    // alignment (global loads need none here) instead of eight or four.
-    __builtin_memcpy(&v, p, 16);
-  } else {
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-    if (E == 8) {
-      const uint16_t* q = reinterpret_cast<const uint16_t*>(p);
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (k + e < d) w[e >> 1] |= (uint32_t)q[e] << (16 * (e & 1));
-    } else {
-      const uint32_t* q = reinterpret_cast<const uint32_t*>(p);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (k + e < d) w[e] = q[e];
-    }
-    v = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-  return v;
-}
+// How a tile's 16-byte chunks are loaded: LD_VEC (widths that are multiples of
+// 16 bytes), LD_ANY (other widths of at least 16 bytes; global loads need no
+// alignment) and LD_SHORT (widths below 16 bytes, element by element).
+enum LoadMode : int { LD_VEC = 0, LD_ANY = 1, LD_SHORT = 2 };
 
-template <typename TIn, bool VEC>
+// Chunks of a 128-row x BK tile of a row-major matrix with rows of length ld, of
+// whose columns the first d (from X) belong to the tile. The loads are
+// unconditional: a chunk outside the tile loads one inside (its row's last) and
+// is cleared by mend_tile_rows. With branches around them the compiler waits
+// for each load in turn.
+template <typename TIn, int LD>
 __device__ __forceinline__ void load_tile_rows(const TIn* X, int64_t ld, int rows_valid, int k0,
                                                int d, uint4 (&r)[4]) {
   constexpr int E = TileCfg<TIn>::E;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int c = threadIdx.x + kThreads * u;
-    r[u] = load_chunk<TIn, VEC>(X, ld, c >> 3, rows_valid, k0 + (c & 7) * E, d);
+    const int row = min(c >> 3, rows_valid - 1), k = k0 + (c & 7) * E;
+    const TIn* p = X + (int64_t)row * ld;
+    if (LD == LD_SHORT) {
+      uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (k + e < d) {
+          if (E == 8) w[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t*>(p)[k + e] << (16 * (e & 1));
+          else w[e] = reinterpret_cast<const uint32_t*>(p)[k + e];
+        }
+      r[u] = make_uint4(w[0], w[1], w[2], w[3]);
+    } else {
+      __builtin_memcpy(&r[u], p + min(k, d - E), 16);
+    }
+  }
+}
+
+// Clears what lies outside the tile (uniform branches: whole tiles skip them).
+template <typename TIn, int LD>
+__device__ __forceinline__ void mend_tile_rows(int rows_valid, int k0, int d, uint4 (&r)[4]) {
+  constexpr int E = TileCfg<TIn>::E;
+  if (k0 + TileCfg<TIn>::BK > d && LD != LD_SHORT) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      // The chunk was loaded `over` elements early.
+      const int over = max(0, k0 + (((int)threadIdx.x + kThreads * u) & 7) * E + E - d);
+      r[u] = LD == LD_VEC ? (over > 0 ? make_uint4(0u, 0u, 0u, 0u) : r[u])
+                          : shift_chunk<(int)sizeof(TIn)>(r[u], over);
+    }
+  }
+  if (rows_valid < kTile) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if ((((int)threadIdx.x + kThreads * u) >> 3) >= rows_valid) r[u] = make_uint4(0u, 0u, 0u, 0u);
   }
 }
 
@@ -127,9 +138,12 @@ __device__ __forceinline__ void store_tile_rows(TIn* Xs, const uint4 (&r)[4]) {
   }
 }
 
-// acc = Xp[rows_p] Xq[rows_q]^T over k in [0, d) of rows of length ld,
-// double-buffered through LDS.
-template <typename TIn, bool VEC>
+// acc = Xp[rows_p] Xq[rows_q]^T over k in [0, d) of rows of length ld. Slice s is
+// multiplied while slice s + 1 waits in registers and slice s + 2 is on its way.
+// Load latency bounds the short row blocks: 640 -> 1295 at B = 16, T = 437 in bf16
+// 51 us with branches around the loads and one slice ahead, 38 us so; 768 ->
+// 50257 at B = 4, T = 128 36.6 and 30.3 us.
+template <typename TIn, int LD>
 __device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int64_t ld, int d,
                                            int rows_p, int rows_q, bool diag,
                                            f32x4_t (&acc)[4][4],
@@ -141,33 +155,45 @@ __device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int64_t
   const int wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int nsteps = (d + BK - 1) / BK;
-  uint4 rp[4], rq[4];
+  struct Slice {
+    uint4 p[4], q[4];
+  };
+  Slice S0, S1;
   zero_acc(acc);
-  load_tile_rows<TIn, VEC>(Xp, ld, rows_p, 0, d, rp);
-  if (!diag) load_tile_rows<TIn, VEC>(Xq, ld, rows_q, 0, d, rq);
-  store_tile_rows<TIn>(lds, rp);
-  if (!diag) store_tile_rows<TIn>(lds + OPE, rq);
-  __syncthreads();
-  for (int s = 0; s < nsteps; ++s) {
-    const int cur = s & 1;
-    const bool more = s + 1 < nsteps;
-    if (more) {
-      load_tile_rows<TIn, VEC>(Xp, ld, rows_p, (s + 1) * BK, d, rp);
-      if (!diag) load_tile_rows<TIn, VEC>(Xq, ld, rows_q, (s + 1) * BK, d, rq);
+  // (Slices past the end load columns of the last one and are not used.)
+  auto fetch = [&](int s, Slice& S) {
+    const int k0 = min(s, nsteps - 1) * BK;
+    load_tile_rows<TIn, LD>(Xp, ld, rows_p, k0, d, S.p);
+    if (!diag) load_tile_rows<TIn, LD>(Xq, ld, rows_q, k0, d, S.q);
+  };
+  auto commit = [&](int s, Slice& S, int buf) {
+    TIn* N = lds + buf * 2 * OPE;
+    mend_tile_rows<TIn, LD>(rows_p, s * BK, d, S.p);
+    store_tile_rows<TIn>(N, S.p);
+    if (!diag) {
+      mend_tile_rows<TIn, LD>(rows_q, s * BK, d, S.q);
+      store_tile_rows<TIn>(N + OPE, S.q);
     }
+  };
+  auto body = [&](int s, int cur, Slice& next, Slice& after) {
+    fetch(s + 2, after);
     const TIn* P = lds + cur * 2 * OPE;
     const TIn* Q = diag ? P : P + OPE;
     mma_step(P + wm * 64 * SK, Q + wn * 64 * SK, acc, lane);
-    if (more) {
-      TIn* N = lds + (cur ^ 1) * 2 * OPE;
-      store_tile_rows<TIn>(N, rp);
-      if (!diag) store_tile_rows<TIn>(N + OPE, rq);
-    }
+    if (s + 1 < nsteps) commit(s + 1, next, cur ^ 1);
     __syncthreads();
+  };
+  fetch(0, S0);
+  fetch(1, S1);
+  commit(0, S0, 0);
+  __syncthreads();
+  for (int s = 0; s < nsteps; s += 2) {
+    body(s, 0, S1, S0);
+    if (s + 1 < nsteps) body(s + 1, 1, S0, S1);
   }
 }
 
-template <typename TIn, bool VEC>
+template <typename TIn, int LD>
 __global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
   constexpr int OPE = lds_operand_elems<TIn>();
   __shared__ __attribute__((aligned(16))) TIn lds[2 * 2 * OPE];
@@ -197,9 +223,9 @@ __global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
   const TIn* G = static_cast<const TIn*>(E.G) + i * (int64_t)E.T * E.d_out;
 
   f32x4_t accA[4][4], accG[4][4];
-  gram_phase<TIn, VEC>(A + (int64_t)p * kTile * E.d_in, A + (int64_t)q * kTile * E.d_in, E.d_in,
+  gram_phase<TIn, LD>(A + (int64_t)p * kTile * E.d_in, A + (int64_t)q * kTile * E.d_in, E.d_in,
                        E.d_in, rows_p, rows_q, diag, accA, lds);
-  gram_phase<TIn, VEC>(G + (int64_t)p * kTile * E.d_out, G + (int64_t)q * kTile * E.d_out, E.d_out,
+  gram_phase<TIn, LD>(G + (int64_t)p * kTile * E.d_out, G + (int64_t)q * kTile * E.d_out, E.d_out,
                        E.d_out, rows_p, rows_q, diag, accG, lds);
   float s = 0.f;
 #pragma unroll
@@ -256,7 +282,7 @@ __device__ __forceinline__ void tile_pair(int nt, int pr, int* p, int* q) {
   *q = pp + rem;
 }
 
-template <typename TIn, bool VEC>
+template <typename TIn, int LD>
 __global__ __launch_bounds__(kThreads, 2) void ghost_part_kernel(GsArgs args) {
   constexpr int OPE = lds_operand_elems<TIn>();
   constexpr int BK = TileCfg<TIn>::BK;
@@ -278,7 +304,7 @@ __global__ __launch_bounds__(kThreads, 2) void ghost_part_kernel(GsArgs args) {
   const int k1 = min((int)((int64_t)slices * (pi + 1) / np) * BK, d);
   const TIn* X = static_cast<const TIn*>(is_a ? E.A : E.G) + i * (int64_t)E.T * d + k0;
   f32x4_t acc[4][4];
-  gram_phase<TIn, VEC>(X + (int64_t)p * kTile * d, X + (int64_t)q * kTile * d, d, k1 - k0,
+  gram_phase<TIn, LD>(X + (int64_t)p * kTile * d, X + (int64_t)q * kTile * d, d, k1 - k0,
                        min(kTile, E.T - p * kTile), min(kTile, E.T - q * kTile), p == q, acc, lds);
   float* dst = args.park + (int64_t)blockIdx.x * kGsTileFloats + 4 * threadIdx.x;
 #pragma unroll
@@ -450,7 +476,7 @@ int launch_t1_group(const dpsgd_layer* layers, const int* idx, int n, const int6
   return DPSGD_OK;
 }
 
-template <typename TIn, bool VEC>
+template <typename TIn, int LD>
 int launch_ghost_group(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
                        float* partials, int64_t P, hipStream_t stream) {
   for (int base = 0; base < n; base += kMaxLayersPerLaunch) {
@@ -475,18 +501,19 @@ int launch_ghost_group(const dpsgd_layer* layers, const int* idx, int n, const i
       wgs += L.B * (int64_t)E.pairs;
     }
     if (wgs > 0x7FFFFFFF) return DPSGD_ERR_INVALID_ARG;
-    hipLaunchKernelGGL((ghost_kernel<TIn, VEC>), dim3((uint32_t)wgs), dim3(kThreads), 0, stream,
+    hipLaunchKernelGGL((ghost_kernel<TIn, LD>), dim3((uint32_t)wgs), dim3(kThreads), 0, stream,
                        args);
     if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
   }
   return DPSGD_OK;
 }
 
-// Every row starts 16-byte aligned (the ABI requires aligned A and G).
+// (The ABI requires 16-byte aligned A and G.)
 template <typename TIn>
-bool ghost_vec_ok(const dpsgd_layer& L) {
+LoadMode ghost_load_mode(const dpsgd_layer& L) {
   constexpr int E = TileCfg<TIn>::E;
-  return L.d_in % E == 0 && L.d_out % E == 0;
+  if (L.d_in % E == 0 && L.d_out % E == 0) return LD_VEC;
+  return L.d_in >= E && L.d_out >= E ? LD_ANY : LD_SHORT;
 }
 
 // Parts of a split layer's A and G columns when a part takes `chunk` slices.
@@ -520,7 +547,7 @@ int64_t gs_chunk(const dpsgd_layer* layers, const int* idx, int n) {
   return lo;
 }
 
-template <typename TIn, bool VEC>
+template <typename TIn, int LD>
 int launch_ghost_split(const dpsgd_layer* layers, const int* idx, int n, int64_t chunk,
                        const int64_t* cols, float* partials, int64_t P, float* park,
                        hipStream_t stream) {
@@ -551,7 +578,7 @@ int launch_ghost_split(const dpsgd_layer* layers, const int* idx, int n, int64_t
       jobs += gs_tiles(L) * E.parts;
       tiles += gs_tiles(L);
     }
-    hipLaunchKernelGGL((ghost_part_kernel<TIn, VEC>), dim3((uint32_t)jobs), dim3(kThreads), 0,
+    hipLaunchKernelGGL((ghost_part_kernel<TIn, LD>), dim3((uint32_t)jobs), dim3(kThreads), 0,
                        stream, args);
     if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
     hipLaunchKernelGGL(ghost_part_combine_kernel, dim3((uint32_t)(tiles * kGsChunks)),
@@ -567,21 +594,20 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
                        hipStream_t stream) {
   const int64_t B = layers[0].B;
   int idx_t1[256], n_t1 = 0;
-  int idx_gv[256], n_gv = 0;
-  int idx_gs[256], n_gs = 0;
+  int idx_gm[3][256], n_gm[3];   // general tiles, by load mode
   int idx_gd[256], n_gd = 0;
   int idx_g4[256], n_g4 = 0;
   int idx_g64[256], n_g64 = 0;
   int idx_mat[256], n_mat = 0;
-  int idx_sv[256], n_sv = 0;
-  int idx_ss[256], n_ss = 0;
+  int idx_sm[3][256], n_sm[3];   // split tiles, by load mode
   // The part size is planned over all split layers of the call.
   std::vector<int> split;
   for (int l = 0; l < n_layers; ++l)
     if (forms[l] == FORM_GHOST_SPLIT) split.push_back(l);
   const int64_t chunk = split.empty() ? 0 : gs_chunk(layers, split.data(), (int)split.size());
   for (int base = 0; base < n_layers; base += 256) {
-    n_t1 = n_gv = n_gs = n_gd = n_g4 = n_g64 = n_mat = n_sv = n_ss = 0;
+    n_t1 = n_gd = n_g4 = n_g64 = n_mat = 0;
+    for (int g = 0; g < 3; ++g) n_gm[g] = n_sm[g] = 0;
     const int m = n_layers - base < 256 ? n_layers - base : 256;
     for (int k = 0; k < m; ++k) {
       const int l = base + k;
@@ -590,28 +616,27 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
         case FORM_STORED: break;   // skinny.hip
         case FORM_GHOST256: idx_g4[n_g4++] = l; break;
         case FORM_GHOST_SPLIT:
-          if (ghost_vec_ok<TIn>(layers[l])) idx_sv[n_sv++] = l;
-          else idx_ss[n_ss++] = l;
+          idx_sm[ghost_load_mode<TIn>(layers[l])][n_sm[ghost_load_mode<TIn>(layers[l])]++] = l;
           break;
         case FORM_GHOST:
           if (ghost_dma_ok(layers[l])) idx_gd[n_gd++] = l;
           else if (gram64_ok(layers[l])) idx_g64[n_g64++] = l;
-          else if (ghost_vec_ok<TIn>(layers[l])) idx_gv[n_gv++] = l;
-          else idx_gs[n_gs++] = l;
+          else idx_gm[ghost_load_mode<TIn>(layers[l])][n_gm[ghost_load_mode<TIn>(layers[l])]++] = l;
           break;
         default: idx_mat[n_mat++] = l; break;
       }
     }
     int st = DPSGD_OK;
     if (n_t1) st = launch_t1_group<TIn>(layers, idx_t1, n_t1, cols, partials, P, B, stream);
-    if (st == DPSGD_OK && n_gv)
-      st = launch_ghost_group<TIn, true>(layers, idx_gv, n_gv, cols, partials, P, stream);
-    if (st == DPSGD_OK && n_gs)
-      st = launch_ghost_group<TIn, false>(layers, idx_gs, n_gs, cols, partials, P, stream);
-    if (st == DPSGD_OK && n_sv)
-      st = launch_ghost_split<TIn, true>(layers, idx_sv, n_sv, chunk, cols, partials, P, park, stream);
-    if (st == DPSGD_OK && n_ss)
-      st = launch_ghost_split<TIn, false>(layers, idx_ss, n_ss, chunk, cols, partials, P, park, stream);
+#define DPSGD_GHOST(LD_)                                                                           \
+  if (st == DPSGD_OK && n_gm[LD_])                                                                \
+    st = launch_ghost_group<TIn, LD_>(layers, idx_gm[LD_], n_gm[LD_], cols, partials, P, stream); \
+  if (st == DPSGD_OK && n_sm[LD_])                                                                \
+  st = launch_ghost_split<TIn, LD_>(layers, idx_sm[LD_], n_sm[LD_], chunk, cols, partials, P, park, stream)
+    DPSGD_GHOST(LD_VEC);
+    DPSGD_GHOST(LD_ANY);
+    DPSGD_GHOST(LD_SHORT);
+#undef DPSGD_GHOST
     if (st == DPSGD_OK && n_gd) st = launch_ghost_dma(layers, idx_gd, n_gd, cols, partials, P, stream);
     if (st == DPSGD_OK && n_g4)
       st = launch_ghost256(layers, idx_g4, n_g4, cols, partials, P, park, stream);
