@@ -118,7 +118,9 @@ size_t dpsgd_norms_workspace_bytes(const dpsgd_layer* layers, int32_t n_layers, 
  * DPSGD_NORM_AUTO: DPSGD_NORM_CLOSED_FORM for T = 1 (under every mode),
  * otherwise DPSGD_NORM_GHOST or DPSGD_NORM_MATERIALIZE; or a negative
  * dpsgd_status for an invalid descriptor. (In dpsgd_clipped_sum_multi a
- * layer with a narrow side may take the stored form instead; see there.) */
+ * layer with a narrow side may take the stored form instead; see there. In a
+ * call whose partials together exceed DPSGD_NOALLOC_SCRATCH_BYTES a float32
+ * layer reported as materialised may run the Gram form.) */
 int32_t dpsgd_select_norm_mode(const dpsgd_layer* layer);
 
 int dpsgd_per_example_norms(const dpsgd_layer* layer, int32_t mode, float* norms_sq,

@@ -68,6 +68,21 @@ NormForm planned_form(const dpsgd_layer& L, NormForm f, bool park_ok) {
   return f == FORM_GHOST && park_ok && ghost256_ok(L) ? FORM_GHOST256 : f;
 }
 
+// Moves Gram-form layers to the materialised form where that is faster. Its
+// partials (one per tile) can be more than the Gram form's (one per tile pair):
+// calls whose partials would not fit the allocation-free call's scratch keep the
+// Gram form, whichever entry point runs them.
+void materialise_faster(const dpsgd_layer* layers, int32_t n, int32_t mode, NormPlan* p) {
+  std::vector<NormForm> forms = p->forms;
+  int64_t cols = 0;
+  for (int32_t l = 0; l < n; ++l) {
+    if (forms[l] == FORM_GHOST && prefer_materialised(layers[l], mode)) forms[l] = FORM_MAT;
+    cols += norm_partials_per_example(layers[l], forms[l]);
+  }
+  if ((size_t)layers[0].B * (size_t)cols * sizeof(float) <= DPSGD_NOALLOC_SCRATCH_BYTES)
+    p->forms.swap(forms);
+}
+
 // Moves the Gram-form layers of a call with few tiles to the split form, when
 // partials and partial tiles together fit the allocation-free call's scratch
 // (so that it runs the same kernels). Layers that the workspace call runs on
@@ -118,6 +133,7 @@ NormPlan plan_norms(const dpsgd_layer* layers, int32_t n, int32_t mode, bool par
   p.cols.resize(n);
   for (int32_t l = 0; l < n; ++l)
     p.forms[l] = planned_form(layers[l], resolve_norm_form(layers[l], mode), park_ok);
+  materialise_faster(layers, n, mode, &p);
   split_few_tiles(layers, n, &p);
   finish_norm_plan(layers, n, &p);
   return p;
@@ -187,6 +203,7 @@ StepPlan plan_step(const dpsgd_layer* layers, int32_t n, int32_t mode) {
         stored ? FORM_STORED : planned_form(layers[l], resolve_norm_form(layers[l], mode), true);
     (stored ? p.stored : p.other).push_back(l);
   }
+  materialise_faster(layers, n, mode, &p.norms);
   split_few_tiles(layers, n, &p.norms);
   finish_norm_plan(layers, n, &p.norms);
   const int64_t B = layers[0].B;
@@ -268,7 +285,7 @@ size_t dpsgd_norms_workspace_bytes(const dpsgd_layer* layers, int32_t n_layers, 
 int32_t dpsgd_select_norm_mode(const dpsgd_layer* layer) {
   const int st = check_layer(layer, false);
   if (st != DPSGD_OK) return st;
-  switch (resolve_norm_form(*layer, DPSGD_NORM_AUTO)) {
+  switch (plan_norms(layer, 1, DPSGD_NORM_AUTO, false).forms[0]) {
     case FORM_T1: return DPSGD_NORM_CLOSED_FORM;
     case FORM_MAT: return DPSGD_NORM_MATERIALIZE;
     default: return DPSGD_NORM_GHOST;

@@ -109,6 +109,8 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // chosen form writes.
 int64_t norm_partials_per_example(const dpsgd_layer& L, NormForm form);
 NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode);
+// Whether AUTO prefers the materialised form for a layer that resolves to Gram.
+bool prefer_materialised(const dpsgd_layer& L, int32_t mode);
 
 // Writes per-example partials partials[i * P + col_l + j] for the given layers
 // (all with the chosen forms), then reduces them into norms_sq. park: the

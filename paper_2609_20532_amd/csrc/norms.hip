@@ -669,11 +669,9 @@ size_t ghost_split_park_bytes(const dpsgd_layer* layers, const int* idx, int n) 
   return (size_t)gs_jobs(layers, idx, n, gs_chunk(layers, idx, n)) * kGsTileFloats * sizeof(float);
 }
 
-NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode) {
-  if (L.T == 1) return FORM_T1;
-  if (mode == DPSGD_NORM_GHOST) return FORM_GHOST;
-  if (mode == DPSGD_NORM_MATERIALIZE) return FORM_MAT;
-  // AUTO: compare the MFMA work each form issues at tile granularity.
+// Gram form where it issues less MFMA work than the materialised one, at tile
+// granularity; work of the Gram kernels counts `weight` times.
+static bool gram_is_less(const dpsgd_layer& L, double weight, int64_t mat_bk) {
   const int64_t bk = L.dtype == DPSGD_BF16 ? TileCfg<uint16_t>::BK : TileCfg<float>::BK;
   const int64_t nt = ceil_div(L.T, kTile);
   // (The float32 kernel for T <= 64 takes one 64 x 64 tile: a quarter of the
@@ -682,8 +680,27 @@ NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode) {
                                     : (double)(nt * (nt + 1) / 2) *
                                           (double)(ceil_div(L.d_in, bk) * bk + ceil_div(L.d_out, bk) * bk);
   const double mt = (double)any_tiles(L) * any_tile_area(L) / (kTile * kTile);
-  const double mat = mt * (double)(ceil_div(L.T, bk) * bk);
-  return ghost <= mat ? FORM_GHOST : FORM_MAT;
+  return ghost * weight <= mt * (double)(ceil_div(L.T, mat_bk) * mat_bk);
+}
+
+NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode) {
+  if (L.T == 1) return FORM_T1;
+  if (mode == DPSGD_NORM_GHOST) return FORM_GHOST;
+  if (mode == DPSGD_NORM_MATERIALIZE) return FORM_MAT;
+  return gram_is_less(L, 1.0, L.dtype == DPSGD_BF16 ? TileCfg<uint16_t>::BK : TileCfg<float>::BK)
+             ? FORM_GHOST
+             : FORM_MAT;
+}
+
+// The float32 Gram kernels multiply on the float32 matrix cores (about 60 of 157
+// TFLOP/s of issued work), the materialised form as products of bf16 parts (about
+// 155), so AUTO weighs the Gram work 2.5 times: 768 -> 3072 at B = 8, T = 512 283 us
+// in Gram form, 119 materialised; 1000 -> 1000 at B = 32, T = 200 154 and 85; just
+// on the Gram side of the line, 512 -> 1536 at B = 123, T = 128 140 and 146. The
+// T <= 64 kernel keeps the plain comparison.
+bool prefer_materialised(const dpsgd_layer& L, int32_t mode) {
+  return mode == DPSGD_NORM_AUTO && L.dtype == DPSGD_F32 && L.T > 1 && !gram64_ok(L) &&
+         !gram_is_less(L, 2.5, TileCfg<float>::BK);
 }
 
 int64_t norm_partials_per_example(const dpsgd_layer& L, NormForm form) {
