@@ -87,9 +87,9 @@ __global__ __launch_bounds__(kThreads) void split_reduce_kernel(SplitArgs args) 
 // those that take more than one MFMA tile (one side of at most two columns).
 // The other small layers run on MFMA tiles, though these stay mostly empty: a
 // 16 x 27 stem convolution at T = 1024, B = 256 in float32 took 114 us here for
-// the norms and 119 us for the sum. The norm variant sums g_i's squares per example; the clip variant
-// adds c_i g_i to the job's partial sum (an example with c_i = 0 is skipped,
-// its rows are never read).
+// the norms and 119 us for the sum. The norm variant sums g_i's squares per
+// example; the clip variant adds c_i g_i to the job's partial sum (an example
+// with c_i = 0 is skipped, its rows are never read).
 
 constexpr int kTinyMaxOut = 2 * kThreads;     // d_in * d_out
 constexpr int kTinyLdsFloats = 16384;         // 64 KB of staged rows

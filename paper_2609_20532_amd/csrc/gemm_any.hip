@@ -33,11 +33,13 @@
 // What bounds it: the matrix cores and, next to them, the conversion on the
 // VALU (5.5 instructions an element), so the loads' addresses cost one
 // instruction each (a scalar base and a fixed 32-bit lane offset).
-// The sixteen convolutions of WRN-16-4 (B = 256, T = 1024, 256 and 64): norms
-// of the materialised ones 1.42 -> 1.00 ms and clipped sums 2.06 -> 1.33 ms
-// against k-major float32 MFMAs (two accumulator sets included, which cost 10 %
-// but bring the error against float64 from 2.1e-6 to 4.4e-7; 6.5e-7 before).
-// bf16, T = 1 (768 -> 768 and 768 -> 10, B = 2048): 72 -> 27 us.
+// The sixteen convolutions of WRN-16-4 (B = 256, T = 1024, 256 and 64; 343
+// GFLOP in all): norms of the materialised ones 1.53 -> 1.05 ms and clipped
+// sums 2.18 -> 1.44 ms against float32 MFMAs, the whole call 3.91 -> 2.46 ms
+// (two accumulator sets included, which cost 10 % but bring the error against
+// float64 from 2.1e-6 to 4.6e-7; 6.7e-7 before). A launch of 137 GFLOP takes
+// 0.89 ms: with six products each 0.93 PFLOP/s at 1.5 GHz, the power limit.
+// bf16, T = 1 (768 -> 768 and 768 -> 10, B = 2048): 72 -> 19 us.
 //
 // Clip weights. FLAT (float32, and bf16 with short or badly padded T): rows
 // run on through the batch and the weight is multiplied into G on the way to
