@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
 // the workspace, in register order (64 KB, 16 bytes a lane), and a second
 // kernel adds a tile's parts in order, multiplies GA by GG and sums. 768 ->
 // 50257 in bf16 with B = 4, T = 128: 4.6 ms with one workgroup a tile (four in
-// all), 30 us split (norms and clipped sum together 6.91 -> 0.13 ms, half of the
+// all), 30 us split (norms and clipped sum together 6.91 -> 0.12 ms, most of the
 // rest in the sum's kernel). At most kGsMaxJobs parts run, so that the partial tiles fit the
 // allocation-free call's scratch and both calls run the same kernels.
 
