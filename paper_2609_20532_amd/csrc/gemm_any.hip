@@ -502,7 +502,8 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
   };
 
   // Norms, at the end of an example: this wave's share of ||G_i^T A_i||_F^2
-  // over the tile (entries past the edges are exactly 0).
+  // over the tile. Entries past the edges are 0 for finite inputs, but 0 times
+  // an infinity is not, so they are cleared when the sum is not finite.
   auto sum_squares = [&]() {
     float s = 0.f;
     auto square = [&]() {
@@ -517,24 +518,27 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
     };
     add_low();
     square();
-    if constexpr (C::kF32) {
-      if (inside && !(s < __builtin_inff())) {
+    if (inside && !(s < __builtin_inff())) {
+      if constexpr (C::kF32)
         recompute_f32<C::kMB, C::kNB>(reinterpret_cast<const float*>(Gb),
                                       reinterpret_cast<const float*>(Ab), M, N, m_base, n_base,
                                       (int64_t)ex * T, (int64_t)(ex + 1) * T, T, nullptr, nullptr,
                                       0.f, acc);
-        // Outside the matrix 0 times an infinity is no zero.
+      // (The lane index is made here and the conditions are sign bits: otherwise
+      // the compiler keeps them in hundreds of scalar registers across the loop.)
+      int li;
+      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(li));
+      const int rows = M - 1 - m_base - 4 * (li >> 5), cols = N - 1 - n_base - (li & 31);
 #pragma unroll
-        for (int a = 0; a < C::kMB; ++a)
+      for (int a = 0; a < C::kMB; ++a)
 #pragma unroll
-          for (int b = 0; b < C::kNB; ++b)
+        for (int b = 0; b < C::kNB; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-              if (m_base + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3) >= M ||
-                  n_base + 32 * b + (lane & 31) >= N)
-                acc[a][b][v] = 0.f;
-        square();
-      }
+          for (int v = 0; v < 16; ++v) {
+            const int past = ((rows - 32 * a - 8 * (v >> 2) - (v & 3)) | (cols - 32 * b)) >> 31;
+            acc[a][b][v] = __int_as_float(__float_as_int(acc[a][b][v]) & ~past);
+          }
+      square();
     }
     clear();
     return s;

@@ -116,3 +116,33 @@ def test_float32_infinities(dp, T, d_in, d_out):
     np.testing.assert_array_equal(S[:, col], ref[:, col])
     keep = np.delete(np.arange(d_in), col)
     assert_sum_close(S[:, keep], ref[:, keep], 2e-6, "finite entries")
+
+
+@pytest.mark.parametrize("T,d_in,d_out", [(64, 16, 16), (128, 27, 16), (100, 130, 70), (80, 9, 200)])
+def test_bf16_infinities(dp, T, d_in, d_out):
+    """bf16 tiles that are partly padding: an infinity in one example gives that
+    example an infinite norm and factor 0, and the sum of the others is what it
+    is without the example (padded entries are 0 x inf and do not count)."""
+    import torch
+    B, bad = 3, 1
+    h = _host_layer(B, T, d_in, d_out, wl.BF16, 78, 0)
+    half = wl.bf16_bits_from_f32(np.float32([-0.5, 0.5]))
+    h.G[bad] = np.where(h.G[bad] >= 0x8000, half[0], half[1])   # no zeros: no NaN inside the matrix
+    h.A[bad, 2, 7] = wl.bf16_bits_from_f32(np.float32([np.inf]))[0]
+    dev = device_layers([h])
+    L = dev[0][0]
+    assert dp.dpsgd_select_norm_mode(L) == dp.DPSGD_NORM_MATERIALIZE
+    ol, = oracle_layers([h])
+    keep = [0, 2]
+    ref = oracle.per_example_norms_sq([oracle.OracleLayer(ol.A[keep], ol.G[keep], 0)])
+    C = float(np.sqrt(ref.min())) * 0.9
+    for mode in (dp.DPSGD_NORM_MATERIALIZE, dp.DPSGD_NORM_AUTO):
+        buf = dp.alloc_step([L], mode)
+        dp.run_clipped_sum([L], buf, C, mode)
+        torch.cuda.synchronize()
+        nsq = buf.norms_sq.cpu().numpy().astype(np.float64)
+        assert math.isinf(nsq[bad])
+        np.testing.assert_allclose(nsq[keep], ref, rtol=3e-6)
+        assert buf.factors[bad].item() == 0.0 and buf.mask.cpu().tolist() == [1, 1, 1]
+        S = sum(C / np.sqrt(n) * ol.G[i].T @ ol.A[i] for i, n in zip(keep, ref))
+        assert_sum_close(torch_to_float64(buf.grads[0]), S, _bound(wl.BF16, T, d_in, d_out), "sum")
