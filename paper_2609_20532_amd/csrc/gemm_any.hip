@@ -23,13 +23,17 @@
 //
 // float32 on the bf16 matrix cores. A float32 number is the sum of three bf16
 // numbers h + m + l (x rounded to bf16, the rest rounded, the rest of that; 24
-// significand bits, exact but for the smallest numbers). The six products of
+// significand bits). Both operands are multiplied by 2^24 first (G with its
+// clip weight, in one multiplication) and the sums by 2^-48, so that also the
+// smallest number's l is a bf16 number (unscaled, operands below 2^-110 lost
+// their low bits). The six products of
 // weight 2^-18 or more (l h, h l, m m, m h, h m, h h) are accumulated in
 // float32; bf16 products are exact there, and the products left out are below
 // 2^-26 of a term. Six v_mfma_f32_32x32x16_bf16 take the place of eight
 // v_mfma_f32_32x32x2_f32 in 3/8 of the cycles. An infinity has no such parts
-// (inf - inf is NaN, and so is inf times a zero part), so a wave whose result
-// is not finite recomputes its block with float32 MFMAs (recompute_f32).
+// (inf - inf is NaN, and so is inf times a zero part), and operands from 2^103
+// or sums from 2^80 leave the range when scaled, so a wave whose result is not
+// finite recomputes its block with float32 MFMAs (recompute_f32).
 // What bounds it: the matrix cores and, next to them, the conversion on the
 // VALU (5.5 instructions an element), so the loads' addresses cost one
 // instruction each (a scalar base and a fixed 32-bit lane offset).
@@ -67,6 +71,7 @@ enum AnyMode : int { ANY_FLAT = 0, ANY_EX = 1, ANY_SUMSQ = 2 };
 // 64 x 256 tiles the last of 2.25 tiles of 576 columns kept one wave of four
 // busy). Both: waves 2 x 2, eight column blocks of 32, two workgroups per CU.
 constexpr int kAnyPerCu = 2;
+constexpr float kAnyScale = 0x1p24f, kAnyUnscale = 0x1p-48f;   // float32 operands, sums
 constexpr int kAnyBlocks = 8;
 
 template <typename TIn, int SHAPE>
@@ -376,14 +381,12 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
       const bool weigh = MODE == ANY_FLAT && u < C::kLoadsM;
       const int gi = u % C::kWaveGroups, v = u / C::kWaveGroups;
       const uint4 in = S.r[u];
-      const float f = S.w[gi];
+      const float f = C::kF32 ? (weigh ? S.w[gi] * kAnyScale : kAnyScale) : S.w[gi];
       if (C::kF32) {
         float x[4] = {__uint_as_float(in.x), __uint_as_float(in.y), __uint_as_float(in.z),
                       __uint_as_float(in.w)};
-        if (weigh) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] *= f;
-        }
+        for (int e = 0; e < 4; ++e) x[e] *= f;
 #pragma unroll
         for (int part = 0; part < 3; ++part) {
           const uint2 o = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
@@ -445,12 +448,12 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
 #pragma unroll
       for (int b = 0; b < C::kNB; ++b) acc[a][b] *= c;
   };
-  auto add_low = [&]() {
+  auto join_parts = [&]() {
     if constexpr (C::kF32) {
 #pragma unroll
       for (int a = 0; a < C::kMB; ++a)
 #pragma unroll
-        for (int b = 0; b < C::kNB; ++b) acc[a][b] += low[a][b];
+        for (int b = 0; b < C::kNB; ++b) acc[a][b] = (acc[a][b] + low[a][b]) * kAnyUnscale;
     }
   };
   clear();
@@ -516,7 +519,7 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
           for (int v = 0; v < 16; ++v) s = fmaf(acc[a][b][v], acc[a][b][v], s);
       s = wave_sum(s);
     };
-    add_low();
+    join_parts();
     square();
     if (inside && !(s < __builtin_inff())) {
       if constexpr (C::kF32)
@@ -596,7 +599,7 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
   }
 
   if (!inside) return;
-  add_low();
+  join_parts();
   if (MODE == ANY_EX) scale(c_cur);
   if constexpr (C::kF32) {
     float bad = 0.f;   // NaN once an entry is not finite

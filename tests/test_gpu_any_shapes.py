@@ -146,3 +146,35 @@ def test_bf16_infinities(dp, T, d_in, d_out):
         assert buf.factors[bad].item() == 0.0 and buf.mask.cpu().tolist() == [1, 1, 1]
         S = sum(C / np.sqrt(n) * ol.G[i].T @ ol.A[i] for i, n in zip(keep, ref))
         assert_sum_close(torch_to_float64(buf.grads[0]), S, _bound(wl.BF16, T, d_in, d_out), "sum")
+
+
+@pytest.mark.parametrize("exp_a,exp_g", [(-122, 100), (100, -122), (-60, -30), (30, 40), (60, 40)])
+@pytest.mark.parametrize("T,d_in,d_out", [(64, 128, 128), (33, 130, 70), (20, 200, 24)])
+def test_float32_magnitudes(dp, T, d_in, d_out, exp_a, exp_g):
+    """float32 operands near the ends of the float32 range (their lower bf16
+    parts would leave it) keep the accuracy of ordinary ones, in the sums and,
+    where the squares are in range, in the materialised norms."""
+    import torch
+    B = 3
+    h = _host_layer(B, T, d_in, d_out, wl.F32, 79, 0)
+    h.A[:] = np.ldexp(h.A, exp_a)
+    h.G[:] = np.ldexp(h.G, exp_g)
+    (L, A, G), = device_layers([h])
+    ol, = oracle_layers([h])
+    if abs(exp_a + exp_g) < 40:
+        nsq = torch.empty(B, device="cuda")
+        mode = dp.DPSGD_NORM_MATERIALIZE
+        ws = torch.empty(dp.dpsgd_norms_workspace_bytes([L], mode), dtype=torch.uint8, device="cuda")
+        dp.dpsgd_per_example_norms_multi([L], mode, nsq, workspace=ws)
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(nsq.cpu().numpy().astype(np.float64),
+                                   oracle.per_example_norms_sq([ol]), rtol=3e-6)
+    factors = np.float32([0.25, 1.0, 0.01])
+    nsq = torch.from_numpy((1.0 / factors.astype(np.float64) ** 2).astype(np.float32)).cuda()
+    c = np.minimum(1.0, 1.0 / np.sqrt(nsq.cpu().numpy().astype(np.float64)))
+    grad = torch.empty(d_out, d_in, device="cuda")
+    ws = torch.empty(dp.dpsgd_clip_workspace_bytes([L]), dtype=torch.uint8, device="cuda")
+    dp.dpsgd_clip_accumulate(L, nsq, 1.0, grad, workspace=ws)
+    torch.cuda.synchronize()
+    S = sum(c[i] * ol.G[i].T @ ol.A[i] for i in range(B))
+    assert rel_err(torch_to_float64(grad), S) <= 2e-6
