@@ -388,15 +388,15 @@ struct T1SumArgs {
   float* norms_sq;
 };
 
-// Sum of squares of n elements at p (any alignment), over the wave's lanes.
+// Sum of squares of n elements at p (any alignment), over the wave's lanes. A
+// wave walks its example alone, so four loads are in flight: three 4096 -> 4096
+// layers in float32 at B = 128 25.4 us with one, 10.0 with four (9.5 for the two
+// kernels above).
 template <typename TIn>
 __device__ __forceinline__ float t1_sum_sq(const TIn* p, int n, int lane) {
-  constexpr int E = 16 / (int)sizeof(TIn);
+  constexpr int E = 16 / (int)sizeof(TIn), kStep = 64 * E, kU = 4;
   float s = 0.f;
-  int e = lane * E;
-  for (; e + E <= n; e += 64 * E) {
-    uint4 v;
-    __builtin_memcpy(&v, p + e, 16);
+  auto add = [&](const uint4& v) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -407,6 +407,19 @@ __device__ __forceinline__ float t1_sum_sq(const TIn* p, int n, int lane) {
         s = fmaf(__uint_as_float(w[k]), __uint_as_float(w[k]), s);
       }
     }
+  };
+  int64_t e = lane * E;
+  for (; e + (kU - 1) * kStep + E <= n; e += kU * kStep) {
+    uint4 v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) __builtin_memcpy(&v[u], p + e + u * kStep, 16);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) add(v[u]);
+  }
+  for (; e + E <= n; e += kStep) {
+    uint4 v;
+    __builtin_memcpy(&v, p + e, 16);
+    add(v);
   }
   for (int k = 0; k < E - 1; ++k)
     if (e + k < n) {
