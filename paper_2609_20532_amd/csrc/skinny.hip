@@ -264,13 +264,12 @@ __global__ __launch_bounds__(kThreads, 3) void skinny_mfma_kernel(SkArgs args) {
   const int g = lane >> 4, cl = lane & 15;
   const int col = chunk * kSkmCols + 8 * cl;
   const bool col_ok = col < d_w;   // d_w % 8 == 0: all eight columns or none
-  // Row t of the example is row i T + t of the tensor; `ahead` rows remain from
-  // row t0 on (loads past them are clamped into the tensor and then cleared).
+  // The range has nr rows; loads past them are clamped to its last row, which is
+  // in the cache, and then cleared.
+  const int nr = t1 - t0;
   const uint32_t stride = 2u * (uint32_t)d_w, nstride = 2u * (uint32_t)r;
   const char* Wb = static_cast<const char*>(E.wide) + (i * T + t0) * (int64_t)stride;
   const char* Nb = static_cast<const char*>(E.narrow) + (i * T + t0) * (int64_t)nstride;
-  const int64_t ahead64 = ((int64_t)args.B - i) * T - t0;
-  const int ahead = (int)(ahead64 < 0x3FFFFFFF ? ahead64 : 0x3FFFFFFF);
   const uint32_t woff = 8u * g * stride + 2u * (uint32_t)(col_ok ? col : 0);
   const bool n_ok = cl < r;
   char* const nbuf = nlds + wave * 1024;
@@ -291,15 +290,15 @@ __global__ __launch_bounds__(kThreads, 3) void skinny_mfma_kernel(SkArgs args) {
   uint32_t nv[8];   // !QUADS
   uint2 nq[2];      // QUADS
   auto load = [&](int tr) {   // rows t0 + tr .. + 31
-    // Row bases and offsets stay inside the tensor: the lanes of load kk reach
+    // Row bases and offsets stay inside the range: the lanes of load kk reach
     // 24 rows and one row's bytes further.
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-      const int row = min(tr + kk, ahead - 1);
-      const uint32_t end = (uint32_t)min(ahead - row, 25) * stride - 16u;
+      const int row = min(tr + kk, nr - 1);
+      const uint32_t end = (uint32_t)min(nr - row, 25) * stride - 16u;
       wv[kk] = *reinterpret_cast<const uint4*>(Wb + (uint64_t)(uint32_t)row * stride + min(woff, end));
     }
-    const int nrow = min(tr, ahead - 1), left = ahead - nrow;
+    const int nrow = min(tr, nr - 1), left = nr - nrow;
     if (QUADS) {
       // 8-byte chunk c of the run of 32 rows: 8 r chunks.
       const uint64_t base = (uint64_t)(uint32_t)nrow * nstride;
@@ -315,14 +314,13 @@ __global__ __launch_bounds__(kThreads, 3) void skinny_mfma_kernel(SkArgs args) {
       }
     }
   };
-  const int nr = t1 - t0;
   load(0);
-  for (int tr = 0; tr < nr; tr += 32) {
+  auto block = [&](int tr, auto last) {
     const int rows = nr - tr;   // valid rows of this block
-    if (rows < 32 || !col_ok) {
+    if (last.value || !col_ok) {
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk)
-        if (8 * g + kk >= rows || !col_ok) wv[kk] = make_uint4(0u, 0u, 0u, 0u);
+        if ((last.value && 8 * g + kk >= rows) || !col_ok) wv[kk] = make_uint4(0u, 0u, 0u, 0u);
     }
     // Transpose the 8 x 8 block: word q of operand j packs rows 2q and
     // 2q + 1 of column j (the low halves of word j / 2 for even j, the high
@@ -342,7 +340,7 @@ __global__ __launch_bounds__(kThreads, 3) void skinny_mfma_kernel(SkArgs args) {
     }
     bf16x8_t a;
     if (QUADS) {
-      if (rows < 32) {
+      if (last.value) {
         const uint32_t valid = (uint32_t)rows * (uint32_t)(r >> 2);
         if ((uint32_t)lane >= valid) nq[0] = make_uint2(0u, 0u);
         if (64u + (uint32_t)lane >= valid) nq[1] = make_uint2(0u, 0u);
@@ -359,16 +357,19 @@ __global__ __launch_bounds__(kThreads, 3) void skinny_mfma_kernel(SkArgs args) {
     } else {
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk)
-        if (!n_ok || 8 * g + kk >= rows) nv[kk] = 0u;
+        if (!n_ok || (last.value && 8 * g + kk >= rows)) nv[kk] = 0u;
       a = skm_bits(nv[0] | (nv[1] << 16), nv[2] | (nv[3] << 16), nv[4] | (nv[5] << 16),
                    nv[6] | (nv[7] << 16));
     }
-    load(tr + 32);
+    if (!last.value) load(tr + 32);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
           a, skm_bits(c[j][0], c[j][1], c[j][2], c[j][3]), acc[j], 0, 0, 0);
-  }
+  };
+  int tr = 0;
+  for (; tr + 32 < nr; tr += 32) block(tr, std::false_type{});
+  block(tr, std::true_type{});
 
   // Output v of MFMA j in lane l: g row m = 4 (l / 16) + v, wide column
   // chunk * 128 + 8 (l % 16) + j.
