@@ -16,6 +16,7 @@
 // multiplied element-wise and summed. Each tile writes one float partial;
 // a final fixed-order reduction adds the partials of every layer of the call
 // into norms_sq, so the result does not depend on scheduling.
+#include <algorithm>
 #include <vector>
 
 #include "mma.h"
@@ -64,7 +65,7 @@ struct GhostEntry {
   int32_t pairs;       // nt (nt + 1) / 2 upper-triangle tile pairs
   uint32_t wg_begin;   // first workgroup of this layer in the launch
   int32_t partial_col;
-  int32_t pad;
+  int32_t load;        // LoadMode
 };
 struct GhostArgs {
   GhostEntry L[kMaxLayersPerLaunch];
@@ -74,35 +75,42 @@ struct GhostArgs {
 };
 
 // How a tile's 16-byte chunks are loaded: LD_VEC (widths that are multiples of
-// 16 bytes), LD_ANY (other widths of at least 16 bytes; global loads need no
-// alignment) and LD_SHORT (widths below 16 bytes, element by element).
-enum LoadMode : int { LD_VEC = 0, LD_ANY = 1, LD_SHORT = 2 };
+// 16 bytes) and LD_ANY (other widths of at least 16 bytes; global loads need no
+// alignment) unconditionally and two slices ahead; LD_FEW (widths as LD_VEC's
+// that make few slices) and LD_SHORT (widths below 16 bytes, element by element)
+// only where the tile has data, and one slice ahead.
+enum LoadMode : int { LD_VEC = 0, LD_ANY = 1, LD_FEW = 2, LD_SHORT = 3 };
 
 // Chunks of a 128-row x BK tile of a row-major matrix with rows of length ld, of
-// whose columns the first d (from X) belong to the tile. The loads are
-// unconditional: a chunk outside the tile loads one inside (its row's last) and
-// is cleared by mend_tile_rows. With branches around them the compiler waits
-// for each load in turn.
+// whose columns the first d (from X) belong to the tile. LD_VEC and LD_ANY: a
+// chunk outside the tile loads one inside (its row's last) and is cleared by
+// mend_tile_rows; with branches around the loads the compiler waits for each in
+// turn.
 template <typename TIn, int LD>
 __device__ __forceinline__ void load_tile_rows(const TIn* X, int64_t ld, int rows_valid, int k0,
                                                int d, uint4 (&r)[4]) {
   constexpr int E = TileCfg<TIn>::E;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int c = threadIdx.x + kThreads * u;
-    const int row = min(c >> 3, rows_valid - 1), k = k0 + (c & 7) * E;
-    const TIn* p = X + (int64_t)row * ld;
-    if (LD == LD_SHORT) {
+    const int c = threadIdx.x + kThreads * u, row = c >> 3, k = k0 + (c & 7) * E;
+    if (LD == LD_VEC || LD == LD_ANY) {
+      __builtin_memcpy(&r[u], X + (int64_t)min(row, rows_valid - 1) * ld + min(k, d - E), 16);
+      continue;
+    }
+    r[u] = make_uint4(0u, 0u, 0u, 0u);
+    if (row >= rows_valid) continue;
+    const TIn* p = X + (int64_t)row * ld + k;
+    if (LD == LD_FEW) {
+      if (k < d) r[u] = *reinterpret_cast<const uint4*>(p);
+    } else {
       uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
       for (int e = 0; e < E; ++e)
         if (k + e < d) {
-          if (E == 8) w[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t*>(p)[k + e] << (16 * (e & 1));
-          else w[e] = reinterpret_cast<const uint32_t*>(p)[k + e];
+          if (E == 8) w[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t*>(p)[e] << (16 * (e & 1));
+          else w[e] = reinterpret_cast<const uint32_t*>(p)[e];
         }
       r[u] = make_uint4(w[0], w[1], w[2], w[3]);
-    } else {
-      __builtin_memcpy(&r[u], p + min(k, d - E), 16);
     }
   }
 }
@@ -111,7 +119,8 @@ __device__ __forceinline__ void load_tile_rows(const TIn* X, int64_t ld, int row
 template <typename TIn, int LD>
 __device__ __forceinline__ void mend_tile_rows(int rows_valid, int k0, int d, uint4 (&r)[4]) {
   constexpr int E = TileCfg<TIn>::E;
-  if (k0 + TileCfg<TIn>::BK > d && LD != LD_SHORT) {
+  if (LD == LD_FEW || LD == LD_SHORT) return;
+  if (k0 + TileCfg<TIn>::BK > d) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       // The chunk was loaded `over` elements early.
@@ -160,9 +169,7 @@ __device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int64_t
   };
   Slice S0, S1;
   zero_acc(acc);
-  // (Slices past the end load columns of the last one and are not used.)
-  auto fetch = [&](int s, Slice& S) {
-    const int k0 = min(s, nsteps - 1) * BK;
+  auto fetch = [&](int k0, Slice& S) {
     load_tile_rows<TIn, LD>(Xp, ld, rows_p, k0, d, S.p);
     if (!diag) load_tile_rows<TIn, LD>(Xq, ld, rows_q, k0, d, S.q);
   };
@@ -175,16 +182,33 @@ __device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int64_t
       store_tile_rows<TIn>(N + OPE, S.q);
     }
   };
-  auto body = [&](int s, int cur, Slice& next, Slice& after) {
-    fetch(s + 2, after);
+  auto multiply = [&](int cur) {
     const TIn* P = lds + cur * 2 * OPE;
     const TIn* Q = diag ? P : P + OPE;
     mma_step(P + wm * 64 * SK, Q + wn * 64 * SK, acc, lane);
+  };
+  fetch(0, S0);
+  if (LD == LD_FEW || LD == LD_SHORT) {   // one slice ahead
+    commit(0, S0, 0);
+    __syncthreads();
+    for (int s = 0; s < nsteps; ++s) {
+      const bool more = s + 1 < nsteps;
+      if (more) fetch((s + 1) * BK, S0);
+      multiply(s & 1);
+      if (more) commit(s + 1, S0, (s & 1) ^ 1);
+      __syncthreads();
+    }
+    return;
+  }
+  // (Slices past the end load columns of the last one and are not used: a branch
+  // around the loads would make the compiler wait for all of them.)
+  auto body = [&](int s, int cur, Slice& next, Slice& after) {
+    fetch(min(s + 2, nsteps - 1) * BK, after);
+    multiply(cur);
     if (s + 1 < nsteps) commit(s + 1, next, cur ^ 1);
     __syncthreads();
   };
-  fetch(0, S0);
-  fetch(1, S1);
+  fetch(BK, S1);
   commit(0, S0, 0);
   __syncthreads();
   for (int s = 0; s < nsteps; s += 2) {
@@ -193,22 +217,10 @@ __device__ __forceinline__ void gram_phase(const TIn* Xp, const TIn* Xq, int64_t
   }
 }
 
+// One tile of a Gram launch.
 template <typename TIn, int LD>
-__global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
-  constexpr int OPE = lds_operand_elems<TIn>();
-  __shared__ __attribute__((aligned(16))) TIn lds[2 * 2 * OPE];
-  __shared__ float red[4];
-
-  int l = 0;
-  {
-    int lo = 0, hi = args.n - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (args.L[mid].wg_begin <= blockIdx.x) lo = mid; else hi = mid - 1;
-    }
-    l = lo;
-  }
-  const GhostEntry& E = args.L[l];
+__device__ __forceinline__ void ghost_tile(const GhostArgs& args, const GhostEntry& E, TIn* lds,
+                                           float* red) {
   const uint32_t w = blockIdx.x - E.wg_begin;
   const int64_t i = w / (uint32_t)E.pairs;
   const int pr = (int)(w % (uint32_t)E.pairs);
@@ -238,6 +250,25 @@ __global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
   if (threadIdx.x == 0) args.partials[i * args.P + E.partial_col + pr] = diag ? s : 2.0f * s;
 }
 
+// Layers of all load modes run in one launch: small layers of one call often
+// differ in it, and launches one after the other cost more than the tiles (24 ->
+// 1 -> 17 -> 10 in float32 at B = 8, T = 256: 22 us with a launch for each mode).
+template <typename TIn>
+__global__ __launch_bounds__(kThreads, 2) void ghost_kernel(GhostArgs args) {
+  __shared__ __attribute__((aligned(16))) TIn lds[2 * 2 * lds_operand_elems<TIn>()];
+  __shared__ float red[4];
+  int lo = 0, hi = args.n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (args.L[mid].wg_begin <= blockIdx.x) lo = mid; else hi = mid - 1;
+  }
+  const GhostEntry& E = args.L[lo];
+  if (E.load == LD_VEC) ghost_tile<TIn, LD_VEC>(args, E, lds, red);
+  else if (E.load == LD_ANY) ghost_tile<TIn, LD_ANY>(args, E, lds, red);
+  else if (E.load == LD_FEW) ghost_tile<TIn, LD_FEW>(args, E, lds, red);
+  else ghost_tile<TIn, LD_SHORT>(args, E, lds, red);
+}
+
 // ------------------------------------------- ghost, tiles split by columns
 //
 // A call with few examples and short sequences has fewer tiles than the GPU
@@ -265,6 +296,7 @@ struct GsEntry {
   uint32_t wg_begin;      // first part job of this layer in the launch
   uint32_t tile_begin;    // first tile of this layer in the launch
   int32_t partial_col;
+  int32_t load;           // LoadMode
 };
 struct GsArgs {
   GsEntry L[kMaxLayersPerLaunch];
@@ -283,13 +315,8 @@ __device__ __forceinline__ void tile_pair(int nt, int pr, int* p, int* q) {
 }
 
 template <typename TIn, int LD>
-__global__ __launch_bounds__(kThreads, 2) void ghost_part_kernel(GsArgs args) {
-  constexpr int OPE = lds_operand_elems<TIn>();
+__device__ __forceinline__ void ghost_part(const GsArgs& args, const GsEntry& E, TIn* lds) {
   constexpr int BK = TileCfg<TIn>::BK;
-  __shared__ __attribute__((aligned(16))) TIn lds[2 * 2 * OPE];
-  int l = 0;
-  while (l + 1 < args.n && args.L[l + 1].wg_begin <= blockIdx.x) ++l;
-  const GsEntry& E = args.L[l];
   const uint32_t w = blockIdx.x - E.wg_begin;
   const int part = (int)(w % (uint32_t)E.parts);
   const uint32_t tile = w / (uint32_t)E.parts;
@@ -312,6 +339,18 @@ __global__ __launch_bounds__(kThreads, 2) void ghost_part_kernel(GsArgs args) {
 #pragma unroll
     for (int b = 0; b < 4; ++b)
       *reinterpret_cast<f32x4_t*>(dst + (4 * a + b) * 4 * kThreads) = acc[a][b];
+}
+
+template <typename TIn>
+__global__ __launch_bounds__(kThreads, 2) void ghost_part_kernel(GsArgs args) {
+  __shared__ __attribute__((aligned(16))) TIn lds[2 * 2 * lds_operand_elems<TIn>()];
+  int l = 0;
+  while (l + 1 < args.n && args.L[l + 1].wg_begin <= blockIdx.x) ++l;
+  const GsEntry& E = args.L[l];
+  if (E.load == LD_VEC) ghost_part<TIn, LD_VEC>(args, E, lds);
+  else if (E.load == LD_ANY) ghost_part<TIn, LD_ANY>(args, E, lds);
+  else if (E.load == LD_FEW) ghost_part<TIn, LD_FEW>(args, E, lds);
+  else ghost_part<TIn, LD_SHORT>(args, E, lds);
 }
 
 // One workgroup per tile and 1/16 of its elements (one float4 a thread).
@@ -489,9 +528,27 @@ int launch_t1_group(const dpsgd_layer* layers, const int* idx, int n, const int6
   return DPSGD_OK;
 }
 
-template <typename TIn, int LD>
-int launch_ghost_group(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
+// (The ABI requires 16-byte aligned A and G.)
+// LD_FEW: up to 384 columns of A and G together (padded to slices). Loads past
+// the last slice are then a good part of all: 64 -> 64 in bf16 at B = 2048, T = 65
+// 21.0 us two slices ahead, 19.3 one; 64 -> 12 in float32 at B = 512 19.7 and 17.7;
+// from about 500 columns on two ahead is as fast or faster.
+template <typename TIn>
+LoadMode ghost_load_mode(const dpsgd_layer& L) {
+  constexpr int E = TileCfg<TIn>::E, BK = TileCfg<TIn>::BK;
+  if (L.d_in < E || L.d_out < E) return LD_SHORT;
+  if (L.d_in % E != 0 || L.d_out % E != 0) return LD_ANY;
+  return (ceil_div(L.d_in, BK) + ceil_div(L.d_out, BK)) * BK <= 384 ? LD_FEW : LD_VEC;
+}
+
+template <typename TIn>
+int launch_ghost_group(const dpsgd_layer* layers, int* idx, int n, const int64_t* cols,
                        float* partials, int64_t P, hipStream_t stream) {
+  // The widest tiles first, so that no CU gets two of them while others have a
+  // narrow one.
+  std::stable_sort(idx, idx + n, [&](int a, int b) {
+    return layers[a].d_in + layers[a].d_out > layers[b].d_in + layers[b].d_out;
+  });
   for (int base = 0; base < n; base += kMaxLayersPerLaunch) {
     const int m = n - base < kMaxLayersPerLaunch ? n - base : kMaxLayersPerLaunch;
     GhostArgs args{};
@@ -511,22 +568,15 @@ int launch_ghost_group(const dpsgd_layer* layers, const int* idx, int n, const i
       E.pairs = E.nt * (E.nt + 1) / 2;
       E.wg_begin = (uint32_t)wgs;
       E.partial_col = (int32_t)cols[idx[base + k]];
+      E.load = ghost_load_mode<TIn>(L);
       wgs += L.B * (int64_t)E.pairs;
     }
     if (wgs > 0x7FFFFFFF) return DPSGD_ERR_INVALID_ARG;
-    hipLaunchKernelGGL((ghost_kernel<TIn, LD>), dim3((uint32_t)wgs), dim3(kThreads), 0, stream,
+    hipLaunchKernelGGL(ghost_kernel<TIn>, dim3((uint32_t)wgs), dim3(kThreads), 0, stream,
                        args);
     if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
   }
   return DPSGD_OK;
-}
-
-// (The ABI requires 16-byte aligned A and G.)
-template <typename TIn>
-LoadMode ghost_load_mode(const dpsgd_layer& L) {
-  constexpr int E = TileCfg<TIn>::E;
-  if (L.d_in % E == 0 && L.d_out % E == 0) return LD_VEC;
-  return L.d_in >= E && L.d_out >= E ? LD_ANY : LD_SHORT;
 }
 
 // Parts of a split layer's A and G columns when a part takes `chunk` slices.
@@ -560,7 +610,7 @@ int64_t gs_chunk(const dpsgd_layer* layers, const int* idx, int n) {
   return lo;
 }
 
-template <typename TIn, int LD>
+template <typename TIn>
 int launch_ghost_split(const dpsgd_layer* layers, const int* idx, int n, int64_t chunk,
                        const int64_t* cols, float* partials, int64_t P, float* park,
                        hipStream_t stream) {
@@ -588,10 +638,11 @@ int launch_ghost_split(const dpsgd_layer* layers, const int* idx, int n, int64_t
       E.wg_begin = (uint32_t)jobs;
       E.tile_begin = (uint32_t)tiles;
       E.partial_col = (int32_t)cols[idx[base + k]];
+      E.load = ghost_load_mode<TIn>(L);
       jobs += gs_tiles(L) * E.parts;
       tiles += gs_tiles(L);
     }
-    hipLaunchKernelGGL((ghost_part_kernel<TIn, LD>), dim3((uint32_t)jobs), dim3(kThreads), 0,
+    hipLaunchKernelGGL(ghost_part_kernel<TIn>, dim3((uint32_t)jobs), dim3(kThreads), 0,
                        stream, args);
     if (check_launch() != DPSGD_OK) return DPSGD_ERR_HIP;
     hipLaunchKernelGGL(ghost_part_combine_kernel, dim3((uint32_t)(tiles * kGsChunks)),
@@ -607,20 +658,19 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
                        hipStream_t stream) {
   const int64_t B = layers[0].B;
   int idx_t1[256], n_t1 = 0;
-  int idx_gm[3][256], n_gm[3];   // general tiles, by load mode
+  int idx_gm[256], n_gm = 0;   // general tiles
   int idx_gd[256], n_gd = 0;
   int idx_g4[256], n_g4 = 0;
   int idx_g64[256], n_g64 = 0;
   int idx_mat[256], n_mat = 0;
-  int idx_sm[3][256], n_sm[3];   // split tiles, by load mode
+  int idx_sm[256], n_sm = 0;   // split tiles
   // The part size is planned over all split layers of the call.
   std::vector<int> split;
   for (int l = 0; l < n_layers; ++l)
     if (forms[l] == FORM_GHOST_SPLIT) split.push_back(l);
   const int64_t chunk = split.empty() ? 0 : gs_chunk(layers, split.data(), (int)split.size());
   for (int base = 0; base < n_layers; base += 256) {
-    n_t1 = n_gd = n_g4 = n_g64 = n_mat = 0;
-    for (int g = 0; g < 3; ++g) n_gm[g] = n_sm[g] = 0;
+    n_t1 = n_gm = n_sm = n_gd = n_g4 = n_g64 = n_mat = 0;
     const int m = n_layers - base < 256 ? n_layers - base : 256;
     for (int k = 0; k < m; ++k) {
       const int l = base + k;
@@ -628,28 +678,21 @@ int launch_norms_typed(const dpsgd_layer* layers, const NormForm* forms, int n_l
         case FORM_T1: idx_t1[n_t1++] = l; break;
         case FORM_STORED: break;   // skinny.hip
         case FORM_GHOST256: idx_g4[n_g4++] = l; break;
-        case FORM_GHOST_SPLIT:
-          idx_sm[ghost_load_mode<TIn>(layers[l])][n_sm[ghost_load_mode<TIn>(layers[l])]++] = l;
-          break;
+        case FORM_GHOST_SPLIT: idx_sm[n_sm++] = l; break;
         case FORM_GHOST:
           if (ghost_dma_ok(layers[l])) idx_gd[n_gd++] = l;
           else if (gram64_ok(layers[l])) idx_g64[n_g64++] = l;
-          else idx_gm[ghost_load_mode<TIn>(layers[l])][n_gm[ghost_load_mode<TIn>(layers[l])]++] = l;
+          else idx_gm[n_gm++] = l;
           break;
         default: idx_mat[n_mat++] = l; break;
       }
     }
     int st = DPSGD_OK;
     if (n_t1) st = launch_t1_group<TIn>(layers, idx_t1, n_t1, cols, partials, P, B, stream);
-#define DPSGD_GHOST(LD_)                                                                           \
-  if (st == DPSGD_OK && n_gm[LD_])                                                                \
-    st = launch_ghost_group<TIn, LD_>(layers, idx_gm[LD_], n_gm[LD_], cols, partials, P, stream); \
-  if (st == DPSGD_OK && n_sm[LD_])                                                                \
-  st = launch_ghost_split<TIn, LD_>(layers, idx_sm[LD_], n_sm[LD_], chunk, cols, partials, P, park, stream)
-    DPSGD_GHOST(LD_VEC);
-    DPSGD_GHOST(LD_ANY);
-    DPSGD_GHOST(LD_SHORT);
-#undef DPSGD_GHOST
+    if (st == DPSGD_OK && n_gm)
+      st = launch_ghost_group<TIn>(layers, idx_gm, n_gm, cols, partials, P, stream);
+    if (st == DPSGD_OK && n_sm)
+      st = launch_ghost_split<TIn>(layers, idx_sm, n_sm, chunk, cols, partials, P, park, stream);
     if (st == DPSGD_OK && n_gd) st = launch_ghost_dma(layers, idx_gd, n_gd, cols, partials, P, stream);
     if (st == DPSGD_OK && n_g4)
       st = launch_ghost256(layers, idx_g4, n_g4, cols, partials, P, park, stream);
