@@ -67,11 +67,33 @@ __global__ __launch_bounds__(kThreads) void split_reduce_kernel(SplitArgs args) 
     }
     *reinterpret_cast<float4*>(E.grad + e) = v;
   } else {
-    for (int k = 0; k < 4 && e + k < E.numel; ++k) {
-      float v = E.accumulate ? E.grad[e + k] : 0.f;
-      for (int s = 0; s < S; ++s) v += E.part[(int64_t)s * E.numel + e + k];
-      E.grad[e + k] = v;
+    // Element loads, 32 in flight (7 -> 70, T = 256, B = 256, 512 splits: 264 us of a
+    // 303 us call with one load at a time).
+    int64_t at[4];
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      at[k] = e + k < E.numel ? e + k : E.numel - 1;
+      v[k] = E.accumulate ? E.grad[at[k]] : 0.f;
     }
+    int s = 0;
+    for (; s + 8 <= S; s += 8) {
+      float p[8][4];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[u][k] = E.part[(int64_t)(s + u) * E.numel + at[k]];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += p[u][k];
+    }
+    for (; s < S; ++s)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] += E.part[(int64_t)s * E.numel + at[k]];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (e + k < E.numel) E.grad[e + k] = v[k];
   }
 }
 
