@@ -205,7 +205,7 @@ struct ClipWeights {
   float* factors_out = nullptr;
   uint8_t* mask_out = nullptr;
 };
-// The layers of one launch have one dtype, any_slow and (clip) weight mode.
+// The layers of one launch have one dtype and (clip) weight mode.
 int launch_any_clip(const dpsgd_layer* layers, const int* idx, int n, const ClipWeights& weights,
                     float* const* outs, const int* splits, const int* accumulate,
                     hipStream_t stream);

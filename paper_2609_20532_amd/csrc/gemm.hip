@@ -273,14 +273,15 @@ int64_t mat_tile_count(const dpsgd_layer& L) {
 namespace {
 
 // Launch of the any-shape kernel that takes a layer (one dtype in a call).
-// Both tile shapes share a launch when the launch is short (a launch costs
-// about 4 us) and have one each when it is long: their slices differ in cost,
-// and a plan of its own fills the rounds better (the convolutions of WRN-16-4,
-// B = 256: 1.46 against 1.42 ms, and half the partial sums).
+// Both tile shapes, and layers with rows below 16 bytes (any_slow) and others,
+// share a launch when the launch is short (a launch costs about 4 us) and have
+// one each when it is long: their slices differ in cost, and a plan of its own
+// fills the rounds better (the convolutions of WRN-16-4, B = 256: 1.46 against
+// 1.42 ms, and half the partial sums).
 constexpr int kAnyGroups = 8;
 constexpr double kMergeFlops = 1.0e10;
 int any_group(const dpsgd_layer& L, bool merge) {
-  return (any_flat(L) ? 0 : 1) + 2 * (any_slow(L) ? 1 : 0) + (merge ? 0 : 4 * any_shape(L));
+  return (any_flat(L) ? 0 : 1) + (merge ? 0 : 2 * (any_slow(L) ? 1 : 0) + 4 * any_shape(L));
 }
 double clip_flops(const dpsgd_layer& L) {
   return 2.0 * (double)(L.B * L.T) * (double)L.d_in * (double)L.d_out;
@@ -507,9 +508,12 @@ int launch_mat_norms(const dpsgd_layer* layers, const int* idx, int n, const int
                      float* partials, int64_t P, hipStream_t stream) {
   const bool bf16 = layers[idx[0]].dtype == DPSGD_BF16;
   int ib[256], it[256], ia[2][256], nb = 0, nt = 0, na[2] = {0, 0};
+  double flops = 0.0;
+  for (int k = 0; k < n; ++k) flops += clip_flops(layers[idx[k]]);
+  const bool merge = flops <= kMergeFlops;
   for (int k = 0; k < n; ++k) {
     const dpsgd_layer& L = layers[idx[k]];
-    const int g = any_slow(L) ? 1 : 0;
+    const int g = any_slow(L) && !merge ? 1 : 0;
     if (tr_tile_ok(L)) ib[nb++] = idx[k];
     else if (tiny_norm_ok(L)) it[nt++] = idx[k];
     else ia[g][na[g]++] = idx[k];

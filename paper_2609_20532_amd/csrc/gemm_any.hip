@@ -106,6 +106,7 @@ struct AnyEntry {
   int32_t accumulate;    // sums, splits == 1: add to grad
   int32_t ex_per_job;    // norms: consecutive examples of one job
   int32_t shape;
+  int32_t slow;          // any_slow
   uint32_t magic;        // FLAT: divides a row by T; otherwise a group by ceil(T / 16)
   int32_t shift;         // -1: the divisor is 1
 };
@@ -654,7 +655,8 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
     }
 }
 
-// Layers of both shapes run in one launch (their LDS is the same size).
+// Layers of both shapes run in one launch (their LDS is the same size); SLOW: so
+// do layers with and without any_slow.
 template <typename TIn, int MODE, bool SLOW, bool NSQ>
 __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs args) {
   using C = AnyCfg<TIn, 0>;
@@ -672,8 +674,13 @@ __global__ __launch_bounds__(kThreads, kAnyPerCu) void tgemm_any_kernel(AnyArgs 
     if (args.L[mid].wg_begin <= blockIdx.x) lo = mid; else hi = mid - 1;
   }
   const AnyEntry& E = args.L[lo];
-  if (E.shape) any_job<TIn, 1, MODE, SLOW, NSQ>(args, E, lds, ended);
-  else any_job<TIn, 0, MODE, SLOW, NSQ>(args, E, lds, ended);
+  if (SLOW && E.slow) {
+    if (E.shape) any_job<TIn, 1, MODE, SLOW, NSQ>(args, E, lds, ended);
+    else any_job<TIn, 0, MODE, SLOW, NSQ>(args, E, lds, ended);
+  } else {
+    if (E.shape) any_job<TIn, 1, MODE, false, NSQ>(args, E, lds, ended);
+    else any_job<TIn, 0, MODE, false, NSQ>(args, E, lds, ended);
+  }
 }
 
 template <typename TIn, int MODE, bool SLOW, bool NSQ>
@@ -702,6 +709,7 @@ int launch_any(const dpsgd_layer* layers, const int* idx, int n, const ClipWeigh
       E.G = L.G;
       E.A = L.A;
       E.shape = any_shape(L);
+      E.slow = any_slow(L) ? 1 : 0;
       E.M = (int32_t)L.d_out;
       E.N = (int32_t)L.d_in;
       E.T = (int32_t)L.T;
@@ -772,11 +780,18 @@ bool any_slow(const dpsgd_layer& L) {
   return std::min(L.d_in, L.d_out) * es < 16 || std::max(L.d_in, L.d_out) * es >= (INT64_C(1) << 28);
 }
 
+// Whether a launch needs the kernel that also takes any_slow layers.
+static bool some_slow(const dpsgd_layer* layers, const int* idx, int n) {
+  bool slow = false;
+  for (int k = 0; k < n; ++k) slow = slow || any_slow(layers[idx[k]]);
+  return slow;
+}
+
 int launch_any_clip(const dpsgd_layer* layers, const int* idx, int n, const ClipWeights& weights,
                     float* const* outs, const int* splits, const int* accumulate,
                     hipStream_t stream) {
   const dpsgd_layer& L = layers[idx[0]];
-  const bool slow = any_slow(L), nsq = weights.norms_sq != nullptr;
+  const bool slow = some_slow(layers, idx, n), nsq = weights.norms_sq != nullptr;
 #define DPSGD_ANY(T_, M_, S_, Q_) \
   launch_any<T_, M_, S_, Q_>(layers, idx, n, weights, outs, splits, accumulate, nullptr, nullptr, 0, stream)
 #define DPSGD_ANY_FLAT(T_)                                                                  \
@@ -795,8 +810,9 @@ int launch_any_norms(const dpsgd_layer* layers, const int* idx, int n, const int
 #define DPSGD_ANY(T_, S_)                                                                         \
   launch_any<T_, ANY_SUMSQ, S_, false>(layers, idx, n, ClipWeights{}, nullptr, nullptr, nullptr, cols, \
                                        partials, P, stream)
-  if (L.dtype == DPSGD_F32) return any_slow(L) ? DPSGD_ANY(float, true) : DPSGD_ANY(float, false);
-  return any_slow(L) ? DPSGD_ANY(uint16_t, true) : DPSGD_ANY(uint16_t, false);
+  const bool slow = some_slow(layers, idx, n);
+  if (L.dtype == DPSGD_F32) return slow ? DPSGD_ANY(float, true) : DPSGD_ANY(float, false);
+  return slow ? DPSGD_ANY(uint16_t, true) : DPSGD_ANY(uint16_t, false);
 #undef DPSGD_ANY
 }
 
