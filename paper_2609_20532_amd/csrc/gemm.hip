@@ -97,21 +97,14 @@ __global__ __launch_bounds__(kThreads) void split_reduce_kernel(SplitArgs args) 
   }
 }
 
-// ------------------------------------------------------------ host side
-
 // ------------------------------------------------------ tiny layers (VALU)
 //
 // Some layers with at most kTinyMaxOut entries in g_i = G_i^T A_i form each
 // example's gradient directly: its rows are staged in LDS a chunk at a time
-// and thread t accumulates entries t and t + 256 of g_i in float32. For the
-// clipped sum these are the bf16 layers with short T, whose weights the MFMA
-// kernel would round to bf16 (here they are applied in float32); for the norms
-// those that take more than one MFMA tile (one side of at most two columns).
-// The other small layers run on MFMA tiles, though these stay mostly empty: a
-// 16 x 27 stem convolution at T = 1024, B = 256 in float32 took 114 us here for
-// the norms and 119 us for the sum. The norm variant sums g_i's squares per
-// example; the clip variant adds c_i g_i to the job's partial sum (an example
-// with c_i = 0 is skipped, its rows are never read).
+// and thread t accumulates entries t and t + 256 of g_i in float32. The norm
+// variant sums g_i's squares per example; the clip variant adds c_i g_i to the
+// job's partial sum (an example with c_i = 0 is skipped, its rows are never
+// read). Which layers: tiny_norm_ok and tiny_clip_ok below.
 
 constexpr int kTinyMaxOut = 2 * kThreads;     // d_in * d_out
 constexpr int kTinyLdsFloats = 16384;         // 64 KB of staged rows
@@ -255,16 +248,41 @@ int launch_tiny_group(const dpsgd_layer* layers, const int* idx, int n, const fl
 
 }  // namespace
 
-bool tiny_clip_ok(const dpsgd_layer& L) {
-  return L.d_in * L.d_out <= kTinyMaxOut && L.dtype == DPSGD_BF16 && any_flat(L);
-}
-bool tiny_norm_ok(const dpsgd_layer& L) {
-  return L.d_in * L.d_out <= kTinyMaxOut && any_tiles(L) > 1;
-}
 int tiny_jobs(const dpsgd_layer& L) {
   // About two workgroups per CU, each over ceil(B / jobs) consecutive examples.
   const int64_t want = L.B < 2 * (int64_t)tr_cu_count() ? L.B : 2 * (int64_t)tr_cu_count();
   return (int)ceil_div(L.B, ceil_div(L.B, want));
+}
+
+// A tiny layer goes to the VALU kernel or to an MFMA tile that stays mostly
+// empty. The VALU kernel's time grows with the entries a thread accumulates (one
+// or two) and the elements it stages, and it runs a workgroup per example; the
+// MFMA kernel takes 16 rows at a time whatever the width, is slower where rows
+// are below 16 bytes (any_slow) and splits long examples.
+bool tiny_norm_ok(const dpsgd_layer& L) {
+  if (L.d_in * L.d_out > kTinyMaxOut) return false;
+  if (any_tiles(L) > 1) return true;
+  // Norm calls in us, VALU and MFMA: float32 16 -> 16, T = 1024, B = 256 67 and 70, 3 -> 16
+  // 59 and 105, 27 -> 16 116 and 70; T = 100, B = 32 16 and 13; T = 4, B = 4096 22 and
+  // 27. bf16 16 -> 16, T = 16, B = 512 9 and 10, T = 64, B = 1024 16 and 12; 3 -> 64
+  // (any_slow), T = 64, B = 1024 21 and 21, T = 256, B = 256 32 and 19; 2 -> 2, T = 1024 52
+  // and 54.
+  if (L.dtype == DPSGD_F32) return L.d_in * L.d_out <= kThreads || L.T < 32;
+  return any_slow(L) ? L.T * (L.d_in + L.d_out) < 4500 : L.T < 16;
+}
+
+bool tiny_clip_ok(const dpsgd_layer& L) {
+  if (L.d_in * L.d_out > kTinyMaxOut) return false;
+  // Clip calls in us, VALU and MFMA: float32 2 -> 2, T = 256, B = 256 28 and 38, 3 -> 16
+  // 30 and 38, 27 -> 16 48 and 40; 2 -> 32 and 32 -> 5, T = 1024 88 and 124; 16 -> 16, T = 64,
+  // B = 1024 39 and 38, T = 1024, B = 16 69 and 21, T = 16, B = 512 31 and 16.
+  if (L.dtype == DPSGD_F32)
+    return L.d_in * L.d_out <= kThreads && L.d_in + L.d_out <= 72 && L.B >= tr_cu_count() &&
+           L.B * L.T >= 32768;
+  // bf16 with the weight on the MFMA operand would round it to bf16. Otherwise:
+  // 3 -> 64, T = 100, B = 32 18 and 23, T = 256, B = 256 45 and 32; 2 -> 2, T = 100, B = 32
+  // 14 and 24, T = 64, B = 1024 34 and 32; 16 -> 16, T = 100, B = 32 15 and 15.
+  return any_flat(L) || (any_slow(L) && L.T <= 300 && L.T * (L.d_in + L.d_out) < 7000 && L.B <= 256);
 }
 int64_t mat_tile_count(const dpsgd_layer& L) {
   return tr_tile_ok(L) ? (L.d_out / 256) * (L.d_in / 256) : any_tiles(L);
@@ -304,6 +322,19 @@ int clip_class(const dpsgd_layer& L) {
                              : 0;
 }
 
+// The same for the layers of a launch.
+void clip_classes(const dpsgd_layer* layers, int n, int8_t* group) {
+  bool any_launch = false;
+  for (int l = 0; l < n; ++l) {
+    group[l] = (int8_t)clip_class(layers[l]);
+    any_launch = any_launch || group[l] == 0;
+  }
+  // Where an any-shape launch runs in any case, a tiny layer joins it (unless its
+  // weights would be rounded there): that costs less than a launch.
+  for (int l = 0; l < n && any_launch; ++l)
+    if (group[l] == kTiny && !(layers[l].dtype == DPSGD_BF16 && any_flat(layers[l]))) group[l] = 0;
+}
+
 }  // namespace
 
 void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
@@ -325,8 +356,8 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   // 300 us.
   constexpr double kMinRaggedFlops = 2.0e10;
   double ragged_flops = 0.0, any_flops = 0.0;
+  clip_classes(layers, n_layers, plan->group);
   for (int l = 0; l < n_layers; ++l) {
-    plan->group[l] = (int8_t)clip_class(layers[l]);
     if (plan->group[l] == kRagged) ragged_flops += clip_flops(layers[l]);
     if (plan->group[l] == 0) any_flops += clip_flops(layers[l]);
   }
@@ -425,13 +456,16 @@ bool clip_from_norms(const dpsgd_layer* layers, int n_layers) {
   // 150 of a float32 slice; a launch for the factors takes about 4 us with its
   // gap. The whole call has to be one launch of any_flat layers.
   constexpr double kMostFlops = 2.0e9;   // about 20 us of the kernel
+  if (n_layers > kMaxLayersPerLaunch) return false;
+  int8_t group[kMaxLayersPerLaunch];
+  clip_classes(layers, n_layers, group);
   double flops = 0.0;
   for (int l = 0; l < n_layers; ++l) {
     const dpsgd_layer& L = layers[l];
-    if (clip_class(L) != 0 || any_group(L, true) != any_group(layers[0], true) || !any_flat(L)) return false;
+    if (group[l] != 0 || any_group(L, true) != any_group(layers[0], true) || !any_flat(L)) return false;
     flops += clip_flops(L);
   }
-  return n_layers <= kMaxLayersPerLaunch && flops <= kMostFlops;
+  return flops <= kMostFlops;
 }
 
 int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const ClipWeights& weights,
@@ -476,8 +510,11 @@ int launch_clip_sum(const dpsgd_layer* layers, int n_layers, const ClipWeights& 
     if (st == DPSGD_OK && cnt[g])
       st = launch_any_clip(layers, idx[g], cnt[g], weights, outs[g], spl[g], acc[g], stream);
   if (st == DPSGD_OK && cnt[kTiny])
-    st = launch_tiny_group<uint16_t, EPI_STORE>(layers, idx[kTiny], cnt[kTiny], factors, outs[kTiny], spl[kTiny], acc[kTiny],
-                                                nullptr, nullptr, 0, stream);
+    st = layers[0].dtype == DPSGD_BF16
+             ? launch_tiny_group<uint16_t, EPI_STORE>(layers, idx[kTiny], cnt[kTiny], factors, outs[kTiny],
+                                                      spl[kTiny], acc[kTiny], nullptr, nullptr, 0, stream)
+             : launch_tiny_group<float, EPI_STORE>(layers, idx[kTiny], cnt[kTiny], factors, outs[kTiny],
+                                                   spl[kTiny], acc[kTiny], nullptr, nullptr, 0, stream);
   if (st != DPSGD_OK) return st;
 
   // Split-K fix-up for the layers that were split.
@@ -511,11 +548,19 @@ int launch_mat_norms(const dpsgd_layer* layers, const int* idx, int n, const int
   double flops = 0.0;
   for (int k = 0; k < n; ++k) flops += clip_flops(layers[idx[k]]);
   const bool merge = flops <= kMergeFlops;
+  // A tiny layer that an MFMA tile covers joins the any-shape launch of a layer
+  // whose examples are at least as long: it ends no later there, and a launch of
+  // the VALU kernel comes on top. (Either way it has one norm partial.)
+  int64_t longest = 0;
+  for (int k = 0; k < n; ++k) {
+    const dpsgd_layer& L = layers[idx[k]];
+    if (!tr_tile_ok(L) && !tiny_norm_ok(L)) longest = std::max(longest, L.T);
+  }
   for (int k = 0; k < n; ++k) {
     const dpsgd_layer& L = layers[idx[k]];
     const int g = any_slow(L) && !merge ? 1 : 0;
     if (tr_tile_ok(L)) ib[nb++] = idx[k];
-    else if (tiny_norm_ok(L)) it[nt++] = idx[k];
+    else if (tiny_norm_ok(L) && !(merge && any_tiles(L) == 1 && L.T <= longest)) it[nt++] = idx[k];
     else ia[g][na[g]++] = idx[k];
   }
   int st = DPSGD_OK;

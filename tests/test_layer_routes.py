@@ -67,3 +67,70 @@ def test_gram_norms_of_every_kind_of_load(dp, dtype, case):
     for k in range(len(dims)):
         check([k])
     check(list(range(len(dims))))
+
+
+def _partial_bytes(B, T, d_in, d_out, dtype):
+    dpsgd.load()
+    L = dpsgd.shape_layer(B, T, d_in, d_out, dtype, 0)
+    return dpsgd.dpsgd_clip_workspace_bytes([L]) - -(-4 * B // 256) * 256
+
+
+@pytest.mark.parametrize("dims,dtype,valu", [
+    ((256, 256, 2, 2), dpsgd.DPSGD_F32, True),        # 28 us, 38 on an MFMA tile
+    ((256, 256, 3, 16), dpsgd.DPSGD_F32, True),
+    ((256, 1024, 64, 3), dpsgd.DPSGD_F32, True),
+    ((256, 256, 27, 16), dpsgd.DPSGD_F32, False),
+    ((16, 1024, 16, 16), dpsgd.DPSGD_F32, False),
+    ((512, 16, 16, 16), dpsgd.DPSGD_F32, False),
+    ((32, 100, 3, 64), dpsgd.DPSGD_BF16, True),       # 18 us, 23
+    ((256, 256, 2, 2), dpsgd.DPSGD_BF16, True),
+    ((512, 16, 16, 16), dpsgd.DPSGD_BF16, True),      # the weight would be rounded
+    ((256, 300, 3, 64), dpsgd.DPSGD_BF16, False),
+    ((32, 100, 16, 16), dpsgd.DPSGD_BF16, False),
+])
+def test_kernel_of_tiny_sums(dims, dtype, valu):
+    """The VALU kernel keeps one partial sum per job of examples (min(B, 512) of
+    them here), the MFMA kernel one per K range."""
+    B, T, d_in, d_out = dims
+    jobs = -(-min(B, 512) * 4 * d_in * d_out // 256) * 256
+    assert (_partial_bytes(*dims, dtype) == jobs) == valu
+
+
+# (dtype, B, [(T, d_in, d_out), ...]): VALU and MFMA kernels, tiny layers that join
+# another's launch, partial sums of entries that are no multiple of 4.
+TINY = [
+    (wl.F32, 256, [(128, 2, 2), (128, 3, 24)]),
+    (wl.F32, 16, [(300, 16, 16), (300, 27, 16), (100, 7, 70)]),
+    (wl.F32, 8, [(31, 22, 22), (32, 22, 22), (128, 4, 7), (128, 7, 200)]),
+    (wl.F32, 3, [(20, 1, 500), (40, 257, 1), (33, 7, 35)]),
+    (wl.BF16, 4, [(100, 3, 64), (100, 64, 3)]),
+    (wl.BF16, 4, [(300, 2, 2), (301, 2, 2), (64, 10, 10), (64, 10, 7), (65, 33, 100)]),
+    (wl.BF16, 8, [(5, 10, 24), (15, 16, 16), (16, 16, 16), (17, 65, 10)]),
+    (wl.BF16, 3, [(256, 16, 16), (192, 3, 20), (1024, 7, 70)]),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(TINY)))
+def test_tiny_layers(dp, case):
+    import torch
+    dtype, B, dims = TINY[case]
+    dev, ol = _layers(dtype, B, dims, 11 + case)
+    Ls = [d[0] for d in dev]
+    ref = oracle.per_example_norms_sq(ol)
+    for mode in (dp.DPSGD_NORM_MATERIALIZE, dp.DPSGD_NORM_AUTO):
+        np.testing.assert_allclose(_norms(Ls, mode, B), ref, rtol=2e-5)
+    nsq = torch.from_numpy(ref.astype(np.float32)).cuda()
+    C = float(np.median(np.sqrt(ref))) * 0.9
+    c = np.minimum(1.0, C / np.sqrt(nsq.cpu().numpy().astype(np.float64)))
+    grads = [torch.full((do, di), 0.25, device="cuda") for _, di, do in dims]
+    ws = torch.empty(dp.dpsgd_clip_workspace_bytes(Ls), dtype=torch.uint8, device="cuda")
+    for accumulate in (False, True):
+        dp.dpsgd_clip_accumulate_multi(Ls, nsq, C, grads, accumulate=accumulate, workspace=ws)
+    torch.cuda.synchronize()
+    for k, (T, di, do) in enumerate(dims):
+        S = 2.0 * np.einsum("i,itm,itn->mn", c, ol[k].G, ol[k].A, optimize=True)
+        # float32 sums; bf16 with short T and more than 512 entries rounds c G.
+        flat = dtype == wl.BF16 and di * do > 512 and not ((-T) % 64 * 8 <= T or
+                                                           (T >= 64 and (-T) % 16 * 8 <= T))
+        assert rel_err(torch_to_float64(grads[k]), S) <= (5e-3 if flat else 4e-6), dims[k]
