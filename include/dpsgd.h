@@ -119,7 +119,8 @@ size_t dpsgd_norms_workspace_bytes(const dpsgd_layer* layers, int32_t n_layers, 
  * otherwise DPSGD_NORM_GHOST or DPSGD_NORM_MATERIALIZE; or a negative
  * dpsgd_status for an invalid descriptor. (In dpsgd_clipped_sum_multi a
  * layer with a narrow side may take the stored form instead; see there. In a
- * call whose partials together exceed DPSGD_NOALLOC_SCRATCH_BYTES a float32
+ * call of several layers one near the line may take the form of the others,
+ * and in a call whose partials together exceed DPSGD_NOALLOC_SCRATCH_BYTES a
  * layer reported as materialised may run the Gram form.) */
 int32_t dpsgd_select_norm_mode(const dpsgd_layer* layer);
 

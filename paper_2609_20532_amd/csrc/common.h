@@ -109,7 +109,11 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // chosen form writes.
 int64_t norm_partials_per_example(const dpsgd_layer& L, NormForm form);
 NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode);
-// Whether AUTO prefers the materialised form for a layer that resolves to Gram.
+// For a layer that AUTO resolves to Gram: whether the materialised form is near
+// enough in work to be considered, its estimated time (us, without launches), and
+// whether that is less than the Gram form's.
+bool may_materialise(const dpsgd_layer& L, int32_t mode);
+double mat_us(const dpsgd_layer& L);
 bool prefer_materialised(const dpsgd_layer& L, int32_t mode);
 
 // Writes per-example partials partials[i * P + col_l + j] for the given layers

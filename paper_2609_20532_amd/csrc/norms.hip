@@ -725,9 +725,9 @@ size_t ghost_split_park_bytes(const dpsgd_layer* layers, const int* idx, int n) 
   return (size_t)gs_jobs(layers, idx, n, gs_chunk(layers, idx, n)) * kGsTileFloats * sizeof(float);
 }
 
-// Gram form where it issues less MFMA work than the materialised one, at tile
-// granularity; work of the Gram kernels counts `weight` times.
-static bool gram_is_less(const dpsgd_layer& L, double weight, int64_t mat_bk) {
+// Gram form where it issues less MFMA work than `tiles` materialised tiles of
+// 128 x 128; work of the Gram kernels counts `weight` times.
+static bool gram_is_less(const dpsgd_layer& L, double weight, double tiles) {
   const int64_t bk = L.dtype == DPSGD_BF16 ? TileCfg<uint16_t>::BK : TileCfg<float>::BK;
   const int64_t nt = ceil_div(L.T, kTile);
   // (The float32 kernel for T <= 64 takes one 64 x 64 tile: a quarter of the
@@ -735,28 +735,64 @@ static bool gram_is_less(const dpsgd_layer& L, double weight, int64_t mat_bk) {
   const double ghost = gram64_ok(L) ? (double)(L.d_in + L.d_out) / 4.0
                                     : (double)(nt * (nt + 1) / 2) *
                                           (double)(ceil_div(L.d_in, bk) * bk + ceil_div(L.d_out, bk) * bk);
-  const double mt = (double)any_tiles(L) * any_tile_area(L) / (kTile * kTile);
-  return ghost * weight <= mt * (double)(ceil_div(L.T, mat_bk) * mat_bk);
+  return ghost * weight <= tiles * (double)(ceil_div(L.T, bk) * bk);
+}
+static double any_tiles_128(const dpsgd_layer& L) {
+  return (double)any_tiles(L) * any_tile_area(L) / (kTile * kTile);
 }
 
 NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode) {
   if (L.T == 1) return FORM_T1;
   if (mode == DPSGD_NORM_GHOST) return FORM_GHOST;
   if (mode == DPSGD_NORM_MATERIALIZE) return FORM_MAT;
-  return gram_is_less(L, 1.0, L.dtype == DPSGD_BF16 ? TileCfg<uint16_t>::BK : TileCfg<float>::BK)
-             ? FORM_GHOST
-             : FORM_MAT;
+  const double tiles = gram64_ok(L) ? any_tiles_128(L)
+                                    : (double)(ceil_div(L.d_out, kTile) * ceil_div(L.d_in, kTile));
+  return gram_is_less(L, 1.0, tiles) ? FORM_GHOST : FORM_MAT;
 }
 
-// The float32 Gram kernels multiply on the float32 matrix cores (about 60 of 157
-// TFLOP/s of issued work), the materialised form as products of bf16 parts (about
-// 155), so AUTO weighs the Gram work 2.5 times: 768 -> 3072 at B = 8, T = 512 283 us
-// in Gram form, 119 materialised; 1000 -> 1000 at B = 32, T = 200 154 and 85; just
-// on the Gram side of the line, 512 -> 1536 at B = 123, T = 128 140 and 146. The
-// T <= 64 kernel keeps the plain comparison.
+// Estimated times of the two forms in microseconds, without launches, fitted to
+// 240 layers (B = 8 to 2048, T = 50 to 512, widths 2 to 1152) within about 10 %.
+// Gram: columns of a tile, at one workgroup a CU, then two, then in rounds.
+static double gram_us(const dpsgd_layer& L) {
+  const bool bf16 = L.dtype == DPSGD_BF16;
+  const int64_t bk = bf16 ? TileCfg<uint16_t>::BK : TileCfg<float>::BK, nt = ceil_div(L.T, kTile);
+  const double jobs = (double)(L.B * (nt * (nt + 1) / 2)), cus = (double)tr_cu_count();
+  const double cols = (double)((ceil_div(L.d_in, bk) + ceil_div(L.d_out, bk)) * bk);
+  const double col_us = jobs <= cus ? (bf16 ? 0.018 : 0.066)
+                                    : (bf16 ? 0.022 : 0.13) * std::max(1.0, jobs / (2.0 * cus));
+  return cols * col_us * (any_slow(L) ? (bf16 ? 2.0 : 1.2) : 1.0);
+}
+// Materialised: 16-row groups of a tile alone, or of all tiles with two
+// workgroups a CU; or the VALU kernel's rows (one or two entries a thread,
+// d_in + d_out staged elements).
+double mat_us(const dpsgd_layer& L) {
+  const bool bf16 = L.dtype == DPSGD_BF16;
+  const double slots = 2.0 * tr_cu_count(), groups = (double)ceil_div(L.T, 16);
+  if (tiny_norm_ok(L)) {
+    const double n = L.d_in * L.d_out > kThreads ? 2.0 : 1.0, w = (double)(L.d_in + L.d_out);
+    const double row = (bf16 ? 8.0 + 41.0 * n + w : 6.0 + 41.0 * n + 0.65 * w) / 1024.0;
+    return std::max(1.0, (double)L.B / slots) * (double)L.T * row;
+  }
+  const double alone = (bf16 ? 0.5 : 0.9) * groups;
+  const double full = (bf16 ? 0.8 : 1.4) * (double)L.B * (double)any_tiles(L) * groups / slots;
+  return std::max(alone, full) * (any_slow(L) ? (bf16 ? 2.0 : 1.4) : 1.0);
+}
+
+// Layers near the line, where the tiles' work alone misjudges: float32 up to 2.5
+// times on the Gram side (whose kernels multiply on the float32 matrix cores,
+// the materialised form as products of bf16 parts, but a call with few
+// examples leaves most CUs without a Gram tile), and bf16 with d_out <= 64 (tiles
+// of 3/4 the area). Gram and materialised, us: float32 768 -> 3072 at B = 8, T = 512
+// 283 and 119; 768 -> 256 at B = 64, T = 100 74 and 23; 768 -> 1152 at B = 512, T = 256
+// 757 and 1270; 576 -> 512 at T = 128 141 and 253; bf16 144 -> 12 at B = 2048, T = 65 29
+// and 24; 16 -> 48 19 and 25. The kernels for T <= 64 in float32 and for 256-row tiles keep
+// the plain comparison.
+bool may_materialise(const dpsgd_layer& L, int32_t mode) {
+  if (mode != DPSGD_NORM_AUTO || L.T == 1 || gram64_ok(L) || ghost256_ok(L)) return false;
+  return !gram_is_less(L, L.dtype == DPSGD_F32 ? 2.5 : 1.0, any_tiles_128(L));
+}
 bool prefer_materialised(const dpsgd_layer& L, int32_t mode) {
-  return mode == DPSGD_NORM_AUTO && L.dtype == DPSGD_F32 && L.T > 1 && !gram64_ok(L) &&
-         !gram_is_less(L, 2.5, TileCfg<float>::BK);
+  return may_materialise(L, mode) && mat_us(L) < gram_us(L);
 }
 
 int64_t norm_partials_per_example(const dpsgd_layer& L, NormForm form) {

@@ -134,3 +134,19 @@ def test_tiny_layers(dp, case):
         flat = dtype == wl.BF16 and di * do > 512 and not ((-T) % 64 * 8 <= T or
                                                            (T >= 64 and (-T) % 16 * 8 <= T))
         assert rel_err(torch_to_float64(grads[k]), S) <= (5e-3 if flat else 4e-6), dims[k]
+
+
+@pytest.mark.parametrize("dims,dtype,form", [
+    # Gram and materialised, us: 757 and 1270, 141 and 253, 11 and 21; 283 and 119,
+    # 74 and 23, 19 and 25; 29 and 24.
+    ((512, 256, 768, 1152), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_GHOST),
+    ((512, 128, 576, 512), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_GHOST),
+    ((64, 256, 12, 32), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_GHOST),
+    ((8, 512, 768, 3072), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_MATERIALIZE),
+    ((64, 100, 768, 256), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_MATERIALIZE),
+    ((2048, 65, 16, 48), dpsgd.DPSGD_BF16, dpsgd.DPSGD_NORM_GHOST),
+    ((2048, 65, 144, 12), dpsgd.DPSGD_BF16, dpsgd.DPSGD_NORM_MATERIALIZE),
+])
+def test_auto_takes_the_faster_norm_form(dims, dtype, form):
+    dpsgd.load()
+    assert dpsgd.dpsgd_select_norm_mode(dpsgd.shape_layer(*dims, dtype, 0)) == form

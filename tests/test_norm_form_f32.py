@@ -21,8 +21,8 @@ def _shape(B, T, d_in, d_out, dtype):
     ((123, 128, 512, 1536), dpsgd.DPSGD_NORM_GHOST),
     ((64, 8, 770, 3072), dpsgd.DPSGD_NORM_MATERIALIZE),
     ((256, 64, 1152, 256), dpsgd.DPSGD_NORM_GHOST),          # the T <= 64 Gram kernel
-    ((800, 450, 768, 50257), dpsgd.DPSGD_NORM_MATERIALIZE),  # 2358 partials an example: 7.5 MB
-    ((900, 450, 768, 50257), dpsgd.DPSGD_NORM_GHOST),        # 8.5 MB of partials
+    ((1700, 450, 384, 50257), dpsgd.DPSGD_NORM_MATERIALIZE),  # 1179 partials an example: 8.0 MB
+    ((1800, 450, 384, 50257), dpsgd.DPSGD_NORM_GHOST),        # 8.5 MB of partials
 ])
 def test_auto_form_of_float32_layers(dims, form):
     dpsgd.load()
