@@ -271,6 +271,7 @@ int launch_wide_clip(const dpsgd_layer* layers, const int* idx, int n, const flo
 // The same tiles for layers that neither large-tile kernel takes: any T from 57
 // on, widths that are multiples of 8.
 bool wide_ragged_ok(const dpsgd_layer& L);
+int64_t wide_tiles(const dpsgd_layer& L);
 int launch_tr_mat_norms(const dpsgd_layer* layers, const int* idx, int n, const int64_t* cols,
                         float* partials, int64_t P, hipStream_t stream);
 

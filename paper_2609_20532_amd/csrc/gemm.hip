@@ -353,15 +353,24 @@ void plan_clip(const dpsgd_layer* layers, int n_layers, ClipPlan* plan) {
   // single layers of 8, 10, 12 and 13 GFLOP took 37.9, 38.9, 42.9 and 45.3 us
   // against 35.3, 36.6, 42.9 and 41.1 on the any-shape kernel, layers of 29,
   // 33, 48 and 164 GFLOP 72.9, 64.1, 79.5 and 180 against 79.2, 72.7, 98.9 and
-  // 300 us.
+  // 300 us. With fewer than nine tiles the launch has too few ranges for the CUs,
+  // or ranges too short for their partial tiles: 192 -> 1000 (3 tiles, 25 GFLOP) 164
+  // us and 91, 392 -> 768 (4, 48) 192 and 118, 192 -> 200 (1, 56) 1687 and 178; 1000
+  // -> 520 (8, 96) 215 and 227, 760 -> 776 (9, 66) 144 and 149, 776 -> 776 (12, 36) 88
+  // and 98, 1544 -> 1000 (21, 53) 89 and 131.
   constexpr double kMinRaggedFlops = 2.0e10;
+  constexpr int64_t kMinRaggedTiles = 9;
   double ragged_flops = 0.0, any_flops = 0.0;
+  int64_t ragged_tiles = 0;
   clip_classes(layers, n_layers, plan->group);
   for (int l = 0; l < n_layers; ++l) {
-    if (plan->group[l] == kRagged) ragged_flops += clip_flops(layers[l]);
+    if (plan->group[l] == kRagged) {
+      ragged_flops += clip_flops(layers[l]);
+      ragged_tiles += wide_tiles(layers[l]);
+    }
     if (plan->group[l] == 0) any_flops += clip_flops(layers[l]);
   }
-  const bool ragged = ragged_flops >= kMinRaggedFlops;
+  const bool ragged = ragged_flops >= kMinRaggedFlops && ragged_tiles >= kMinRaggedTiles;
   if (!ragged) any_flops += ragged_flops;
   const bool merge = any_flops <= kMergeFlops;
   int idx[kClipGroups][kMaxLayersPerLaunch], cnt[kClipGroups] = {};

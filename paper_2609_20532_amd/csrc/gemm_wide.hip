@@ -446,6 +446,8 @@ bool wide_tile_ok(const dpsgd_layer& L) {
   return 50 * pad <= 3 * L.d_out && tm * (L.d_in / kWdTN) >= tr_cu_count();
 }
 
+int64_t wide_tiles(const dpsgd_layer& L) { return wide_tiles_m(L) * ceil_div(L.d_in, kWdTN); }
+
 bool wide_ragged_ok(const dpsgd_layer& L) {
   // The widths' 16-byte chunks must not straddle rows; T as any_flat's rule
   // says (weights on the accumulator, at least four groups an example). The
@@ -455,7 +457,7 @@ bool wide_ragged_ok(const dpsgd_layer& L) {
   if (L.dtype != DPSGD_BF16 || wide_tile_ok(L) || tr_tile_ok(L) || any_flat(L)) return false;
   if (L.d_in % 8 != 0 || L.d_out % 8 != 0 || L.d_in > (INT64_C(1) << 24) || L.d_out > (INT64_C(1) << 24))
     return false;
-  const double wide = (double)wide_tiles_m(L) * (double)ceil_div(L.d_in, kWdTN) * kWdTileElems;
+  const double wide = (double)wide_tiles(L) * kWdTileElems;
   return wide * kAnyVsWide <= (double)any_tiles(L) * any_tile_area(L);
 }
 

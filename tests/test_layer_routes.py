@@ -150,3 +150,17 @@ def test_tiny_layers(dp, case):
 def test_auto_takes_the_faster_norm_form(dims, dtype, form):
     dpsgd.load()
     assert dpsgd.dpsgd_select_norm_mode(dpsgd.shape_layer(*dims, dtype, 0)) == form
+
+
+@pytest.mark.parametrize("dims,wide", [
+    ((107, 1000, 256, 200), False),     # one 384 x 256 tile: 212 us there, 40 on 128 x 128
+    ((439, 183, 392, 768), False),      # four
+    ((1024, 64, 192, 1000), False),     # three
+    ((163, 183, 776, 776), True),       # twelve: 88 us and 98
+])
+def test_padded_tiles_need_several_tiles(dims, wide):
+    """Partial sums are 384 x 256 tiles on the padded large tiles, whole sums on
+    the any-shape kernel."""
+    part = _partial_bytes(*dims, dpsgd.DPSGD_BF16)
+    assert (part % (4 * 384 * 256) == 0) == wide
+    assert (part % (4 * dims[2] * dims[3]) == 0) != wide
