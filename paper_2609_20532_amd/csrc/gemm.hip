@@ -67,8 +67,8 @@ __global__ __launch_bounds__(kThreads) void split_reduce_kernel(SplitArgs args) 
     }
     *reinterpret_cast<float4*>(E.grad + e) = v;
   } else {
-    // Element loads, 32 in flight (7 -> 70, T = 256, B = 256, 512 splits: 264 us of a
-    // 303 us call with one load at a time).
+    // Element loads, 32 in flight (7 -> 70, T = 256, B = 256, 512 splits: 302 us a call
+    // with one load at a time, 72 so).
     int64_t at[4];
     float v[4];
 #pragma unroll

@@ -413,12 +413,13 @@ __global__ __launch_bounds__(kThreads) void clip_factors_kernel(const float* __r
   if (i < B) write_factor(norms_sq[i], C, i, factors, factors_out, mask_out);
 }
 
-// Calls of a few layers that all have T = 1: one wave per example takes every
-// layer and writes the squared norm itself, so the call is one launch instead
+// Calls of a few layers that all have T = 1: W waves per example take every
+// layer and write the squared norm themselves, so the call is one launch instead
 // of two (784 -> 512 -> 10, float32, B = 256: one kernel of 4.6 us for two of
 // 3.1 and 2.3 us and the gap between them). With more layers than kT1Layers one
 // workgroup per example and layer and a reduction finish sooner.
 constexpr int kT1Layers = 4;
+constexpr int kT1Waves = kThreads / 64;
 struct T1SumArgs {
   T1Entry L[kT1Layers];
   int32_t n;
@@ -427,13 +428,16 @@ struct T1SumArgs {
   float* norms_sq;
 };
 
-// Sum of squares of n elements at p (any alignment), over the wave's lanes. A
-// wave walks its example alone, so four loads are in flight: three 4096 -> 4096
-// layers in float32 at B = 128 25.4 us with one, 10.0 with four (9.5 for the two
-// kernels above).
-template <typename TIn>
-__device__ __forceinline__ float t1_sum_sq(const TIn* p, int n, int lane) {
-  constexpr int E = 16 / (int)sizeof(TIn), kStep = 64 * E, kU = 4;
+// Wave w's share (of W) of the sum of squares of n elements at p (any alignment),
+// over its lanes. A wave walks its share alone, a kilobyte a load, so four loads
+// are in flight, and examples of 48 KB or more take four waves: three 4096 ->
+// 4096 layers in float32 at B = 128 25.4 us with one load and one wave, 10.0 with
+// four loads, 5.8 with both (7.8 to 9.5 for the two kernels above); with shorter
+// examples one wave is as fast, and faster with many (four 1024 -> 1024 layers in
+// bf16 at B = 8192: 21 us and 35).
+template <typename TIn, int W>
+__device__ __forceinline__ float t1_sum_sq(const TIn* p, int n, int w, int lane) {
+  constexpr int E = 16 / (int)sizeof(TIn), kStep = 64 * E * W, kU = 4;
   float s = 0.f;
   auto add = [&](const uint4& v) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -447,7 +451,7 @@ __device__ __forceinline__ float t1_sum_sq(const TIn* p, int n, int lane) {
       }
     }
   };
-  int64_t e = lane * E;
+  int64_t e = (64 * w + lane) * E;
   for (; e + (kU - 1) * kStep + E <= n; e += kU * kStep) {
     uint4 v[kU];
 #pragma unroll
@@ -468,21 +472,34 @@ __device__ __forceinline__ float t1_sum_sq(const TIn* p, int n, int lane) {
   return s;
 }
 
-template <typename TIn>
+template <typename TIn, int W>
 __global__ __launch_bounds__(kThreads) void t1_sum_kernel(T1SumArgs args) {
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= args.B) return;   // uniform per wave
-  const int lane = threadIdx.x & 63;
+  __shared__ float red[2][W];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t i = W == 1 ? (int64_t)blockIdx.x * kT1Waves + wave : (int64_t)blockIdx.x;
+  if (i >= args.B) return;   // uniform per wave; never with W > 1
+  const int w = W == 1 ? 0 : wave;
   float total = args.accumulate ? args.norms_sq[i] : 0.0f;
   for (int l = 0; l < args.n; ++l) {
     const T1Entry& E = args.L[l];
-    float sa = t1_sum_sq(static_cast<const TIn*>(E.A) + i * E.d_in, E.d_in, lane);
-    float sg = t1_sum_sq(static_cast<const TIn*>(E.G) + i * E.d_out, E.d_out, lane);
+    float sa = t1_sum_sq<TIn, W>(static_cast<const TIn*>(E.A) + i * E.d_in, E.d_in, w, lane);
+    float sg = t1_sum_sq<TIn, W>(static_cast<const TIn*>(E.G) + i * E.d_out, E.d_out, w, lane);
     sa = wave_sum(sa);
     sg = wave_sum(sg);
+    if constexpr (W > 1) {
+      static_assert(W == 4, "four waves' sums");
+      __syncthreads();   // the previous layer's sums are read
+      if (lane == 0) {
+        red[0][w] = sa;
+        red[1][w] = sg;
+      }
+      __syncthreads();
+      sa = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+      sg = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    }
     total = fmaf(sa, sg, total);
   }
-  if (lane == 0) args.norms_sq[i] = total;
+  if (lane == 0 && w == 0) args.norms_sq[i] = total;
 }
 
 template <typename TIn>
@@ -499,8 +516,14 @@ int launch_t1_sum(const dpsgd_layer* layers, int n, float* norms_sq, int accumul
     args.L[l].d_in = (int32_t)layers[l].d_in;
     args.L[l].d_out = (int32_t)layers[l].d_out;
   }
-  hipLaunchKernelGGL(t1_sum_kernel<TIn>, dim3((uint32_t)ceil_div(args.B, 4)), dim3(kThreads), 0, stream,
-                     args);
+  int64_t bytes = 0;   // of an example
+  for (int l = 0; l < n; ++l) bytes += (layers[l].d_in + layers[l].d_out) * (int64_t)sizeof(TIn);
+  if (bytes < (48 << 10))
+    hipLaunchKernelGGL((t1_sum_kernel<TIn, 1>), dim3((uint32_t)ceil_div(args.B, kT1Waves)),
+                       dim3(kThreads), 0, stream, args);
+  else
+    hipLaunchKernelGGL((t1_sum_kernel<TIn, kT1Waves>), dim3((uint32_t)args.B), dim3(kThreads), 0, stream,
+                       args);
   return check_launch();
 }
 
@@ -530,7 +553,7 @@ int launch_t1_group(const dpsgd_layer* layers, const int* idx, int n, const int6
 
 // (The ABI requires 16-byte aligned A and G.)
 // LD_FEW: up to 384 columns of A and G together (padded to slices). Loads past
-// the last slice are then a good part of all: 64 -> 64 in bf16 at B = 2048, T = 65
+// the last slice are then a good part of all: 32 -> 48 in bf16 at B = 2048, T = 65
 // 21.0 us two slices ahead, 19.3 one; 64 -> 12 in float32 at B = 512 19.7 and 17.7;
 // from about 500 columns on two ahead is as fast or faster.
 template <typename TIn>

@@ -31,9 +31,11 @@ def _norms(Ls, mode, B):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
-@pytest.mark.parametrize("widths", [(1, 3), (255, 1020), (1027, 2049), (4096, 771), (4099, 6)])
+@pytest.mark.parametrize("widths", [(1, 3), (255, 1020), (1027, 2049), (4096, 771), (4099, 6),
+                                    (12289, 5), (8200, 4097)])
 def test_t1_norms_at_the_edges_of_their_loads(dp, dtype, widths):
-    """Four loads of a kilobyte a wave, single loads, and the last elements."""
+    """Four loads of a kilobyte a wave, single loads, and the last elements; one
+    wave an example, and four from 48 KB on."""
     B = 5
     dev, ol = _layers(dtype, B, [(1,) + widths, (1,) + widths[::-1]], 3)
     got = _norms([d[0] for d in dev], dp.DPSGD_NORM_AUTO, B)
