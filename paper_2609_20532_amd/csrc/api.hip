@@ -381,13 +381,23 @@ int dpsgd_clip_accumulate_multi(const dpsgd_layer* layers, int32_t n_layers,
   float* partial_base = reinterpret_cast<float*>(
       static_cast<char*>(workspace) + round_up((size_t)B * sizeof(float), kFactorBytesAlign));
   ClipWeights weights;
-  // (An output over the norms themselves is written before the sums start.)
-  const auto overlaps = [&](const void* p, size_t bytes) {
-    const char *a = static_cast<const char*>(p), *n = reinterpret_cast<const char*>(norms_sq);
-    return p && a < n + (size_t)B * sizeof(float) && n < a + bytes;
+  // The sums' kernel may form the factors only where it reads the norms and writes
+  // the factors beside everything else that it writes: a caller may keep the norms
+  // in a gradient's buffer, or let an output lie over them or over a gradient (the
+  // factors are then formed, and written, before the sums start).
+  const auto overlaps = [](const void* a, size_t na, const void* b, size_t nb) {
+    const char *p = static_cast<const char*>(a), *q = static_cast<const char*>(b);
+    return p && q && p < q + nb && q < p + na;
   };
-  if (clip_from_norms(layers, n_layers) && !overlaps(factors_out, (size_t)B * sizeof(float)) &&
-      !overlaps(mask_out, (size_t)B)) {
+  const size_t nf = (size_t)B * sizeof(float);
+  bool apart = !overlaps(factors_out, nf, norms_sq, nf) && !overlaps(mask_out, (size_t)B, norms_sq, nf) &&
+               !overlaps(workspace, need, norms_sq, nf);
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const size_t ng = (size_t)(layers[l].d_in * layers[l].d_out) * sizeof(float);
+    apart = apart && !overlaps(grads[l], ng, norms_sq, nf) && !overlaps(grads[l], ng, factors_out, nf) &&
+            !overlaps(grads[l], ng, mask_out, (size_t)B);
+  }
+  if (clip_from_norms(layers, n_layers) && apart) {
     weights.norms_sq = norms_sq;
     weights.C = C;
     weights.factors_out = factors_out;

@@ -166,3 +166,31 @@ def test_padded_tiles_need_several_tiles(dims, wide):
     part = _partial_bytes(*dims, dpsgd.DPSGD_BF16)
     assert (part % (4 * 384 * 256) == 0) == wide
     assert (part % (4 * dims[2] * dims[3]) == 0) != wide
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["norms", "factors", "mask"])
+def test_norms_or_outputs_inside_a_gradient(dp, where):
+    """The squared norms of a small call may lie in the buffer of a gradient that
+    it writes (they are read before), and an output there is overwritten by it."""
+    import torch
+    B, T, d_in, d_out = 512, 1, 96, 40
+    dev, ol = _layers(wl.F32, B, [(T, d_in, d_out)], 23)
+    L = dev[0][0]
+    n = np.sqrt(oracle.per_example_norms_sq(ol))
+    C = float(np.median(n))
+    grad = torch.empty(d_out, d_in, device="cuda")
+    inside = grad.view(-1)[64:64 + B]
+    nsq = inside if where == "norms" else torch.empty(B, device="cuda")
+    factors = inside if where == "factors" else torch.empty(B, device="cuda")
+    mask = inside.view(torch.uint8)[:B] if where == "mask" else torch.empty(B, dtype=torch.uint8,
+                                                                           device="cuda")
+    nsq.copy_(torch.from_numpy((n * n).astype(np.float32)))
+    ws = torch.empty(dp.dpsgd_clip_workspace_bytes([L]), dtype=torch.uint8, device="cuda")
+    dp.dpsgd_clip_accumulate(L, nsq, C, grad, factors_out=factors, mask_out=mask, workspace=ws)
+    torch.cuda.synchronize()
+    c = np.minimum(1.0, C / n)
+    S = np.einsum("i,itm,itn->mn", c, ol[0].G, ol[0].A)
+    assert rel_err(torch_to_float64(grad), S) <= 2e-6
+    if where != "factors":
+        np.testing.assert_allclose(factors.cpu().numpy(), c, rtol=1e-6)
