@@ -144,6 +144,9 @@ typedef f32x16_t WdAcc[kWdMB][kWdNB];
 template <bool ZA, bool RAGGED>
 __device__ float wd_segment(const WdEntry& E, int tm, int tn, int64_t q0, int64_t q1,
                             const float* factors, char* lds, WdAcc& acc) {
+  // The waits below count kWdCopies instructions a slice; RAGGED slices issue
+  // fewer or more, and only with two slots is the count that is waited for 0.
+  static_assert(!RAGGED || kWdStages == 2, "the copies of a ragged slice are not counted");
   const int M = E.M, N = E.N, T = E.T;
   const int spe = RAGGED ? (T + kWdBK - 1) / kWdBK : T / kWdBK;   // slices per example
   // 32-column blocks of G inside the matrix (12 except in a ragged last row tile).
