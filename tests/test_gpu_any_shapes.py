@@ -11,7 +11,8 @@ import pytest
 import oracle
 from paper_2609_20532_amd import workloads as wl
 
-from parity_util import assert_sum_close, device_layers, oracle_layers, rel_err, torch_to_float64
+from parity_util import (assert_sum_close, device_layers, oracle_layers, rel_err, tile256,
+                         torch_to_float64, wide_tile)
 
 pytestmark = pytest.mark.gpu
 
@@ -26,11 +27,30 @@ CASES = [
     (wl.BF16, 4, [(1, 130, 67), (17, 192, 9), (50, 129, 200)]),          # weight on the operand
     (wl.BF16, 3, [(65, 7, 300), (65, 300, 7), (20, 2, 300), (3, 1, 1)]),    # rows below 16 bytes
     (wl.BF16, 1, [(512, 72, 24)]),
-    # at least 20 GFLOP in all: the 384 x 256 tiles with padding (last row, column
-    # and K slice partly filled; T one row past a slice and one row short of one)
+    # the 384 x 256 tiles with padding (last row, column and K slice partly filled; T
+    # one row past a slice and one row short of one, one partial 16-row group)
     (wl.BF16, 3, [(1025, 1608, 2000), (1000, 512, 392)]),
-    (wl.BF16, 5, [(191, 2040, 3000), (257, 776, 1544), (130, 256, 4104)]),
+    (wl.BF16, 7, [(191, 2040, 3000), (257, 776, 1544), (130, 256, 4104)]),
 ]
+PADDED_TILES = (9, 10)   # of CASES
+
+
+def _takes_padded_tiles(B, dims):
+    """The library's rule for the 384 x 256 tiles with padding, for a bf16 call:
+    every layer eligible (widths that are multiples of 8, weights on the
+    accumulator, not much more tile area than the any-shape kernel's, no other
+    large tile), together at least 20 GFLOP and nine tiles."""
+    tiles = 0
+    for T, di, do in dims:
+        n = -(-do // 384) * -(-di // 256)
+        flat = not ((-T) % 64 * 8 <= T or (T >= 64 and (-T) % 16 * 8 <= T))
+        small = (-(-do // 64) * -(-di // 192) * 64 * 192 if do <= 64
+                 else -(-do // 128) * -(-di // 128) * 128 * 128)
+        if (di % 8 or do % 8 or flat or n * 384 * 256 * 0.62 > small or wide_tile(T, di, do)
+                or tile256(T, di, do)):
+            return False
+        tiles += n
+    return tiles >= 9 and sum(2.0 * B * T * di * do for T, di, do in dims) >= 2e10
 
 
 def _host_layer(B, T, d_in, d_out, dtype, seed, tensor_id):
@@ -55,6 +75,8 @@ def _bound(dtype, T, d_in, d_out):
 def test_sums_and_materialised_norms(dp, case):
     import torch
     dtype, B, dims = CASES[case]
+    if case in PADDED_TILES:
+        assert _takes_padded_tiles(B, dims)
     hs = [_host_layer(B, T, di, do, dtype, 900 + 10 * case + k, k)
           for k, (T, di, do) in enumerate(dims)]
     dev = device_layers(hs)
@@ -178,3 +200,26 @@ def test_float32_magnitudes(dp, T, d_in, d_out, exp_a, exp_g):
     torch.cuda.synchronize()
     S = sum(c[i] * ol.G[i].T @ ol.A[i] for i in range(B))
     assert rel_err(torch_to_float64(grad), S) <= 2e-6
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_padded_tiles_leave_out_examples_of_factor_0(dp, accumulate):
+    """384 x 256 tiles with padding: an example in the middle and the last one have
+    an infinite norm and rows of NaN and infinities; the sum is that of the others."""
+    import torch
+    B, T, d_in, d_out = 4, 1025, 1608, 2104
+    assert _takes_padded_tiles(B, [(T, d_in, d_out)])
+    h = _host_layer(B, T, d_in, d_out, wl.BF16, 80, 0)
+    for i, value in ((1, np.nan), (3, np.inf)):
+        bits = wl.bf16_bits_from_f32(np.float32([value]))[0]
+        h.A[i, ::3], h.G[i, 1::5] = bits, bits
+    (L, A, G), = device_layers([h])
+    ol, = oracle_layers([h])
+    keep = [0, 2]
+    nsq = torch.tensor([4.0, math.inf, 0.25, math.inf], device="cuda")
+    grad = torch.full((d_out, d_in), 0.25, device="cuda")
+    ws = torch.empty(dp.dpsgd_clip_workspace_bytes([L]), dtype=torch.uint8, device="cuda")
+    dp.dpsgd_clip_accumulate(L, nsq, 1.0, grad, accumulate=accumulate, workspace=ws)
+    torch.cuda.synchronize()
+    S = sum(c * ol.G[i].T @ ol.A[i] for i, c in zip(keep, (0.5, 1.0)))
+    assert_sum_close(torch_to_float64(grad), S + (0.25 if accumulate else 0.0), 2e-6, "sum")
