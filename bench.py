@@ -48,18 +48,36 @@ def dominant_kernel(W) -> str:
     rules): bf16 on the 384x256-tile kernel when d_in % 256 == 0, T % 64 == 0 and
     d_out % 384 == 0, or d_out % 32 == 0 with a ragged last row tile padding at
     most 6 % on a layer of at least one tile per CU; else bf16 on the 256x256-tile
-    kernel when both widths are multiples of 256; else the any-shape kernel."""
-    s = max(W.layers, key=lambda s: s.d_in * s.d_out)
+    kernel when both widths are multiples of 256; else, for widths that are
+    multiples of 8, on the 384x256 tiles with padding when the call's layers of
+    that kind make at least 20 GFLOP and nine tiles; else the any-shape kernel."""
+    T, w_pad, a_pad = W.T, (-W.T) % 64, (-W.T) % 16
+    on_accumulator = w_pad * 8 <= T or (T >= 64 and a_pad * 8 <= T)
+
+    def kernel(s):
+        tiles_m, tiles_n = -(-s.d_out // 384), -(-s.d_in // 256)
+        pad = tiles_m * 384 - s.d_out
+        ragged = s.d_out % 32 == 0 and 50 * pad <= 3 * s.d_out and tiles_m * (s.d_in // 256) >= 256
+        if s.d_in % 256 == 0 and T % 64 == 0 and (s.d_out % 384 == 0 or ragged):
+            return "tgemm_wide_kernel<false>"
+        if s.d_in % 256 == 0 and s.d_out % 256 == 0 and T % 32 == 0:
+            return "tgemm_tr_kernel<0>"
+        small = (-(-s.d_out // 64) * -(-s.d_in // 192) * 64 * 192 if s.d_out <= 64
+                 else -(-s.d_out // 128) * -(-s.d_in // 128) * 128 * 128)
+        if (s.d_in % 8 == 0 and s.d_out % 8 == 0 and on_accumulator
+                and 0.62 * tiles_m * tiles_n * 384 * 256 <= small):
+            return "tgemm_wide_kernel<true>"
+        return "tgemm_any_kernel"
+
     if W.dtype != "bf16":
         return "tgemm_any_kernel"
-    tiles_m = -(-s.d_out // 384)
-    pad = tiles_m * 384 - s.d_out
-    ragged = s.d_out % 32 == 0 and 50 * pad <= 3 * s.d_out and tiles_m * (s.d_in // 256) >= 256
-    if s.d_in % 256 == 0 and W.T % 64 == 0 and (s.d_out % 384 == 0 or ragged):
-        return "tgemm_wide_kernel"
-    if s.d_in % 256 == 0 and s.d_out % 256 == 0 and W.T % 32 == 0:
-        return "tgemm_tr_kernel<0>"
-    return "tgemm_any_kernel"
+    name = kernel(max(W.layers, key=lambda s: s.d_in * s.d_out))
+    if name == "tgemm_wide_kernel<true>":
+        padded = [s for s in W.layers if kernel(s) == name]
+        if (sum(2.0 * W.B * T * s.d_in * s.d_out for s in padded) < 2e10
+                or sum(-(-s.d_out // 384) * -(-s.d_in // 256) for s in padded) < 9):
+            name = "tgemm_any_kernel"
+    return name
 
 
 def parse():
@@ -395,7 +413,11 @@ def main():
     t_adamw = time_noise_adamw(dpsgd, Ls, buf, W, scale, args.steps)
     adamw_gbs = work["noise_adamw_bytes"] / (t_adamw * 1e-3) / 1e9
 
-    mfma_peak = PEAK_BF16_TFLOPS if W.dtype == "bf16" else PEAK_FP32_TFLOPS
+    # float32 sums and materialised norms multiply on the bf16 matrix cores, six
+    # products for one; the float32 Gram kernels on the float32 matrix cores.
+    mfma_peak = PEAK_BF16_TFLOPS if W.dtype == "bf16" else PEAK_BF16_TFLOPS / 6.0
+    gram = any(dpsgd.dpsgd_select_norm_mode(L) == dpsgd.DPSGD_NORM_GHOST for L in Ls)
+    norm_peak = PEAK_FP32_TFLOPS if W.dtype != "bf16" and gram else mfma_peak
     clip_tflops = work["clip_flops"] / (t_clip * 1e-3) / 1e12
     norm_tflops = 0.0 if args.fused else work["norm_flops"] / (t_norm * 1e-3) / 1e12
     norm_gbs = 0.0 if args.fused else work["input_bytes"] / (t_norm * 1e-3) / 1e9
@@ -430,6 +452,8 @@ def main():
                           "the split-K tail fix-up)")),
             "achieved": clip_tflops,
             "peak": mfma_peak,
+            "peak_of": ("dense bf16 MFMA" if W.dtype == "bf16" else
+                        "dense bf16 MFMA / 6 (six products of bf16 parts for a float32 one)"),
             "unit": "TFLOP/s",
             "frac": clip_tflops / mfma_peak,
             "traffic": measured_traffic(W.name),
@@ -439,7 +463,7 @@ def main():
             "graph_ms_per_step": graph_ms,
             "norms_ms": None if args.fused else t_norm,
             "norms_tflops": None if args.fused else norm_tflops,
-            "norms_frac_mfma": None if args.fused else norm_tflops / mfma_peak,
+            "norms_frac_mfma": None if args.fused else norm_tflops / norm_peak,
             "norms_input_gbs": None if args.fused else norm_gbs,
             "norms_frac_hbm": None if args.fused else norm_gbs / PEAK_HBM_GBS,
             "clip_ms": t_clip, "clip_tflops": clip_tflops,

@@ -103,8 +103,9 @@ def stored_form(T: int, d_in: int, d_out: int, dtype: str) -> bool:
 def weights_in_fp32(T: int, d_in: int, d_out: int, dtype: str, fused: bool = False) -> bool:
     """True when the library applies every clip weight in float32 on this
     layer (no bfloat16 rounding of c_i * G): float32 inputs; the stored form;
-    layers whose g_i has at most 512 entries (formed on the VALU); the 256-
-    and 384x256-tile kernels; the 128-tile kernel when T needs at most 1/8 of
+    layers whose g_i has at most 512 entries (formed on the VALU where the MFMA
+    kernel would round the weight); the 256-
+    and 384x256-tile kernels; the any-shape kernel when T needs at most 1/8 of
     zero padding to a multiple of its 64-row K step."""
     if dtype == wl.F32:
         return True

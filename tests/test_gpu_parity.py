@@ -122,9 +122,9 @@ NORM_SHAPES = [
     (2, 300, 64, 128),     # three row blocks: single tiles, ragged last block
     (2, 512, 128, 64),     # four row blocks of single tiles
     (2, 520, 64, 192),     # five row blocks, the last one 8 rows
-    (3, 64, 520, 60),      # float32 k-major kernel, 64 x 256 tiles, ragged in both widths
-    (2, 96, 132, 260),     # float32 k-major kernel, 128 x 128 tiles, ragged in both widths
-    (5, 64, 27, 16),       # stem-convolution widths: g_i formed on the VALU
+    (3, 64, 520, 60),      # float32 any-shape kernel, 64 x 192 tiles, ragged in both widths
+    (2, 96, 132, 260),     # float32 any-shape kernel, 128 x 128 tiles, ragged in both widths
+    (5, 64, 27, 16),       # stem-convolution widths: one tile, mostly padding
     (3, 64, 192, 128),     # float32 Gram form on one 64 x 64 tile (T = 64)
     (2, 37, 128, 64),      # the same with rows past T (zeroed in LDS)
 ]
@@ -217,15 +217,15 @@ CLIP_SHAPES = [
     (12, 5, 64, 96, wl.BF16),       # small T: weight applied to the operand
     (4, 70, 13, 21, wl.BF16),       # non-vector loads
     (3, 9, 11, 7, wl.F32),
-    (4, 64, 96, 80, wl.F32),        # float32, T a multiple of the K step: weight on the accumulator
+    (4, 64, 96, 80, wl.F32),        # float32, T a multiple of the slices' rows
     (3, 32, 27, 10, wl.F32),        # the same with element loads (widths not multiples of 4)
-    (3, 40, 30, 25, wl.F32),        # transposing kernel, element loads (g_i above the VALU path's 512)
+    (3, 40, 30, 25, wl.F32),        # the same, T not a multiple (g_i above the VALU path's 512)
     (4, 70, 26, 21, wl.BF16),       # the same for bfloat16
-    (1100, 8, 27, 16, wl.F32),      # VALU path, jobs of 3 consecutive examples
-    (1, 40, 8, 8, wl.F32),          # VALU path, a single job writing the gradient directly
-    (40, 1, 16, 10, wl.F32),        # VALU path, T = 1 (a classifier head)
-    (6, 96, 520, 60, wl.F32),       # float32 k-major kernel: 64 x 256 tiles, ragged, split along K
-    (5, 128, 132, 260, wl.F32),     # float32 k-major kernel: 128 x 128 tiles, ragged
+    (1100, 8, 27, 16, wl.F32),      # one tile, many short examples
+    (1, 40, 8, 8, wl.F32),          # one tile, one K range writing the gradient directly
+    (40, 1, 16, 10, wl.F32),        # T = 1 (a classifier head)
+    (6, 96, 520, 60, wl.F32),       # float32 any-shape kernel: 64 x 192 tiles, ragged, split along K
+    (5, 128, 132, 260, wl.F32),     # float32 any-shape kernel: 128 x 128 tiles, ragged
     (4, 64, 256, 512, wl.BF16),     # 256x256-tile kernel, one split
     (8, 256, 256, 256, wl.BF16),    # 256x256-tile kernel, split along K
     (4, 64, 256, 384, wl.BF16),     # 384x256-tile kernel, one tile split along K

@@ -4,8 +4,8 @@ The paper's CIFAR-10 recipe processes its batch in micro-batches of 512. On
 tensors captured from one forward/backward of WRN-16-4 (random weights and
 images), the step runs as the benchmark runs it (three ABI calls, AUTO norm
 forms: the round-filling split plan with tens of K splits per layer and
-split_reduce_kernel on the k-major float32 kernel, the Gram form for the
-T = 64 convolutions, the VALU path for the stem and the classifier). The
+split_reduce_kernel on the any-shape kernel, the Gram form for the T = 64
+convolutions, the closed form for the classifier). The
 float64 oracle then materialises every example's gradient of every layer, so
 every norm, clip factor and mask bit is checked, and it evaluates the clipped
 sum and the noised output at sampled entries of every layer from their

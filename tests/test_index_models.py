@@ -36,106 +36,179 @@ def test_xcd_two_class_index_is_a_permutation(nwg, n_first):
     assert sorted(jobs) == list(range(nwg))
 
 
-# ------------------------------------- k-major float32 kernel (tgemm_k32_kernel)
-
-K32_ROWS = 32                               # k rows per slice
-K32_STAGE = K32_ROWS * (64 + 256)           # floats of the largest slice (64 x 256 tile)
-K32_MAX_COPIES = K32_STAGE // 256 // 4      # 1 KB copies per wave
+# ------------------------------------ any-shape kernel (tgemm_any_kernel)
 
 
-def k32_tile(M):
-    return (64, 256) if M <= 64 else (128, 128)
+def tr16_reads(elems, addr):
+    """ds_read_b64_tr_b16 of one wave: each group of 16 lanes reads a 4 x 16 block
+    of 2-byte elements, lane s four of row s / 4 at columns 4 (s % 4); lane s gets
+    column s. elems: the LDS as 2-byte elements; addr: the lanes' byte addresses.
+    Returns [64][4]."""
+    assert np.all(addr % 8 == 0) and np.all(addr // 2 + 4 <= elems.size)
+    got = elems[(addr // 2)[:, None] + np.arange(4)]             # [lane][4]
+    block = got.reshape(4, 4, 16)                                # [group][row][column]
+    return block.transpose(0, 2, 1).reshape(64, 4)
 
 
-def k32_slice(G, A, M, N, tmi, tni, q, sumsq):
-    """One slice q of tile (tmi, tni) through the kernel's copies and operand
-    reads. Returns the tile's 32-row product (and checks every access)."""
-    TM, TN = k32_tile(M)
-    nm, ncopy = TM // 8, (TM + TN) // 8
-    assert ncopy <= 4 * K32_MAX_COPIES
-    lds = np.zeros(K32_STAGE, np.float64) if sumsq else np.full(K32_STAGE, np.nan)
+def mfma_32x32x16(g_frag, a_frag):
+    """Lane l supplies row (first operand) or column (second) l % 32 and
+    k = 8 (l / 32) .. + 7."""
+    G, A = np.zeros((32, 16)), np.zeros((16, 32))
+    for half in range(2):
+        G[:, 8 * half:8 * half + 8] = g_frag[32 * half:32 * half + 32]
+        A[8 * half:8 * half + 8, :] = a_frag[32 * half:32 * half + 32].T
+    return G @ A
+
+
+def any_slice(G, A, f32, tm, tn, row0):
+    """One slice from row row0 of tile (tm, tn): loads (every one inside its
+    tensor), shifts and clears, LDS writes (every element written once), transposed
+    reads (a half-wave touches every bank once), MFMAs. Returns the tile."""
+    rows, M = G.shape
+    N = A.shape[1]
+    narrow = M <= 64
+    mb, nb = (1, 3) if narrow else (2, 2)
+    es, bk = (4, 16) if f32 else (2, 64)
+    kE, block = 16 // es, bk // 4 * 256
+    groups = 1 if f32 else 2                       # 16-row groups of a slice one wave loads
+    loads = 8 * 32 * bk * es // 16 // 256
+    loads_m = 2 * mb * 32 * bk * es // 16 // 256
+    per, per_m = loads // groups, loads_m // groups
+    lds = np.full(8 * block // 2, np.nan)
     for wave in range(4):
-        for p in range(K32_MAX_COPIES):
-            c = wave + 4 * p
-            if c >= ncopy:
-                continue
-            mside = c < nm
-            W, R, X = (TM, M, G) if mside else (TN, N, A)
-            lane = np.arange(64)
-            f = 256 * (c if mside else c - nm) + 4 * lane
-            k, pc = f // W, f & (W - 1)
-            col = (tmi * TM if mside else tni * TN) + ((pc + W - 32 * (k & 1)) & (W - 1))
-            voff = k * R * 4 + np.minimum(col, R - 4) * 4
-            assert np.all(voff < 2 ** 32) and np.all(k < K32_ROWS)
-            byte0 = q * K32_ROWS * R * 4 + voff
-            assert np.all(byte0 + 16 <= X.size * 4) and np.all(byte0 % 16 == 0)
-            dst = 1024 * c + 16 * lane
-            assert np.all(dst + 16 <= K32_STAGE * 4)
-            for ln in range(64):
-                if sumsq and col[ln] >= R:
-                    continue          # the norm variant leaves these words at zero
-                b0 = byte0[ln] // 4
-                lds[dst[ln] // 4: dst[ln] // 4 + 4] = X.reshape(-1)[b0:b0 + 4]
-    wc = TN // 64
-    out = np.zeros((TM, TN))
+        for lane in range(64):
+            rl = 8 * (wave & 1) + (lane >> 3)
+            lcol = 32 * (wave >> 1) + 4 * (lane & 7) if f32 else 8 * (lane & 7)
+            for gi in range(groups):
+                first = row0 + 16 * (0 if f32 else (wave >> 1) + 2 * gi)
+                nv = max(0, min(16, rows - first))
+                if nv == 0:
+                    first = 0
+                for v in range(per):
+                    X, width = (G, M) if v < per_m else (A, N)
+                    col = (64 * mb * tm + lcol + 64 * v if v < per_m
+                           else 64 * nb * tn + lcol + 64 * (v - per_m))
+                    off = rl * width + min(col, width - kE)
+                    if rows - first < 16:
+                        off = min(off, (rows - first) * width - kE)
+                    at = first * width + off
+                    assert 0 <= at and at + kE <= X.size
+                    over = max(0, col + kE - width)
+                    x = np.concatenate([X.reshape(-1)[at:at + kE][min(over, kE):],
+                                        np.zeros(min(over, kE))])
+                    if rl >= nv:
+                        x = np.zeros(kE)
+                    if f32:   # one part: 8 bytes a lane
+                        to = (wave >> 1) * block + 512 * (wave & 1) + 8 * lane
+                    else:
+                        odd, rr = (lane >> 2) & 1, (lane >> 3) & 3
+                        to = (odd * block + 256 * (4 * (wave >> 1) + 2 * (wave & 1) + (lane >> 5)) +
+                              64 * ((rr + 2 * odd) & 3) + 16 * (lane & 3))
+                    to = (to + 2 * v * block + gi * 8 * 256) // 2
+                    assert np.isnan(lds[to:to + kE]).all()
+                    lds[to:to + kE] = x
+    assert not np.isnan(lds).any()
+    lane = np.arange(64)
+    g, s = lane >> 4, lane & 15
+
+    def frag(blk, ks):
+        pos = s >> 2 if f32 else ((s >> 2) + 2 * (blk & 1)) & 3
+        addr = blk * block + 512 * (g >> 1) + 32 * (g & 1) + 8 * (s & 3) + 64 * pos + 1024 * ks
+        for half in range(2):
+            banks = addr[32 * half:32 * half + 32] // 4 % 64
+            assert np.unique(banks).size == 32                 # 8 bytes a lane: every bank once
+        return np.concatenate([tr16_reads(lds, addr), tr16_reads(lds, addr + 256)], axis=1)
+
+    out = np.zeros((64 * mb, 64 * nb))
     for wave in range(4):
-        wm, wn = wave // wc, wave % wc
-        for a in range(2):
-            for b in range(2):
-                D = np.zeros((32, 32))
-                lane = np.arange(64)
-                h, c32 = lane >> 5, lane & 31
-                oa = h * TM + ((wm * 64 + 32 * a + 32 * h) & (TM - 1)) + c32
-                ob = K32_ROWS * TM + h * TN + ((wn * 64 + 32 * b + 32 * h) & (TN - 1)) + c32
-                for kp in range(K32_ROWS // 2):
-                    ia, ib = oa + 2 * kp * TM, ob + 2 * kp * TN
-                    assert np.all(ia < K32_ROWS * TM)
-                    assert np.all((K32_ROWS * TM <= ib) & (ib < K32_ROWS * (TM + TN)))
-                    Aop = np.zeros((32, 2))
-                    Bop = np.zeros((2, 32))
-                    Aop[c32, h] = lds[ia]
-                    Bop[h, c32] = lds[ib]
-                    D += Aop @ Bop
-                out[wm * 64 + 32 * a: wm * 64 + 32 * a + 32,
-                    wn * 64 + 32 * b: wn * 64 + 32 * b + 32] = D
+        wm, wn = wave >> 1, wave & 1
+        for ks in range(bk // 16):
+            for a in range(mb):
+                for b in range(nb):
+                    r, c = 32 * (mb * wm + a), 32 * (nb * wn + b)
+                    out[r:r + 32, c:c + 32] += mfma_32x32x16(frag(mb * wm + a, ks),
+                                                             frag(2 * mb + nb * wn + b, ks))
     return out
 
 
-@pytest.mark.parametrize("M,N", [(64, 576), (64, 16), (128, 1152), (12, 100), (100, 36),
-                                 (64, 144), (132, 260), (256, 2304)])
-def test_k32_copies_and_reads_give_the_tile_product(M, N):
-    """Ragged widths, both tile shapes: the clip variant's tile equals
-    G_sliceᵀ A_slice on its valid part, and the norm variant's tile (copies
-    past the edge skipped, words left at zero) has exactly the valid part's
-    sum of squares."""
-    T, B = 64, 2
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("M,N", [(64, 192), (16, 27), (63, 193), (128, 128), (127, 129), (200, 9),
+                                 (9, 200), (65, 130)])
+def test_any_shape_slices_give_the_tile_product(M, N, f32):
     rng = np.random.default_rng(M * 1000 + N)
-    G = rng.standard_normal((B * T, M)).astype(np.float32)
-    A = rng.standard_normal((B * T, N)).astype(np.float32)
-    TM, TN = k32_tile(M)
-    tiles = [(tmi, tni) for tmi in range(-(-M // TM)) for tni in range(-(-N // TN))]
-    if len(tiles) > 6:
-        tiles = tiles[:3] + tiles[-3:]
-    for tmi, tni in tiles:
-        for q in (0, B * T // K32_ROWS - 1):
-            rows = slice(q * K32_ROWS, (q + 1) * K32_ROWS)
-            ref = G[rows].astype(np.float64).T @ A[rows].astype(np.float64)
-            m0, n0 = tmi * TM, tni * TN
-            mv, nv = min(TM, M - m0), min(TN, N - n0)
-            out = k32_slice(G, A, M, N, tmi, tni, q, sumsq=False)
-            assert not np.isnan(out[:mv, :nv]).any()
-            np.testing.assert_allclose(out[:mv, :nv], ref[m0:m0 + mv, n0:n0 + nv], atol=1e-9)
-            sq = k32_slice(G, A, M, N, tmi, tni, q, sumsq=True)
-            assert math.isclose(float(np.sum(sq * sq)),
-                                float(np.sum(ref[m0:m0 + mv, n0:n0 + nv] ** 2)), rel_tol=1e-12)
+    bk = 16 if f32 else 64
+    rows = 2 * bk - 5                                    # the last slice lacks rows
+    G, A = rng.standard_normal((rows, M)), rng.standard_normal((rows, N))
+    tm, tn = (64, 192) if M <= 64 else (128, 128)
+    for i in range(-(-M // tm)):
+        for j in range(-(-N // tn)):
+            for row0 in (0, bk):
+                ref = np.zeros((tm, tn))
+                part = G[row0:row0 + bk].T @ A[row0:row0 + bk]
+                part = part[i * tm:(i + 1) * tm, j * tn:(j + 1) * tn]
+                ref[:part.shape[0], :part.shape[1]] = part
+                np.testing.assert_allclose(any_slice(G, A, f32, i, j, row0), ref, atol=1e-9)
 
 
-def test_k32_every_wave_has_copies():
-    for TM, TN in ((64, 256), (128, 128)):
-        nc = (TM + TN) // 8
-        assert nc * 1024 <= K32_STAGE * 4
-        for wave in range(4):
-            assert sum(1 for p in range(K32_MAX_COPIES) if wave + 4 * p < nc) >= 4
+# ------------------ 384 x 256 tiles with padding (tgemm_wide_kernel<true>)
+
+
+def padded_slice(G, A, T, tm, tn, ex, ls):
+    """Slice ls of example ex: copies (every one inside its tensor and example),
+    transposed reads, MFMAs over the 16-row groups that hold rows."""
+    M, N = G.shape[1], A.shape[1]
+    row = ex * T + 64 * ls
+    nv = T - 64 * ls
+    n16 = (min(64, nv) + 15) // 16 * 16
+    lds = np.full(80 * 1024 // 2, np.nan)
+    lane = np.arange(64)
+    for t in range(80):
+        gs = t < 48
+        u, per = (t, 3) if gs else (t - 48, 2)
+        X, width = (G, M) if gs else (A, N)
+        r0 = 4 * (u // per)
+        if r0 >= n16 and r0 + 4 > nv:
+            continue
+        col = (384 * tm if gs else 256 * tn) + 32 * (4 * (u % per) + (lane >> 4)) + 8 * (lane & 3)
+        off = (r0 + ((lane >> 2) & 3)) * width + np.minimum(col, width - 8)
+        for ln in range(64):
+            to = 512 * t + 8 * ln
+            if r0 + ((ln >> 2) & 3) < nv:
+                at = row * width + off[ln]
+                assert ex * T * width <= at and at + 8 <= (ex + 1) * T * width
+                lds[to:to + 8] = X.reshape(-1)[at:at + 8]
+            else:
+                lds[to:to + 8] = 0.0
+    g, s = lane >> 4, lane & 15
+    unit = 64 * (s >> 2) + 32 * (g & 1) + 8 * (s & 3)
+
+    def frag(base, group, blk, ks):
+        at = [base + (2 * (g >> 1) + h + 4 * ks) * group + 256 * blk + unit for h in range(2)]
+        x = np.concatenate([tr16_reads(lds, a) for a in at], axis=1)
+        assert not np.isnan(x).any()
+        return x
+
+    out = np.zeros((384, 256))
+    for ks in range(min(4, (nv + 15) >> 4)):
+        for i in range(12):
+            for j in range(8):
+                out[32 * i:32 * i + 32, 32 * j:32 * j + 32] += mfma_32x32x16(
+                    frag(0, 3072, i, ks), frag(48 * 1024, 2048, j, ks))
+    return out
+
+
+@pytest.mark.parametrize("T,M,N,tile", [(130, 392, 264, (1, 1)), (191, 384, 512, (0, 1)),
+                                        (57, 776, 248, (2, 0))])
+def test_padded_tiles_copies_and_reads_give_the_tile_product(T, M, N, tile):
+    rng = np.random.default_rng(T)
+    G, A = rng.standard_normal((2 * T, M)), rng.standard_normal((2 * T, N))
+    tm, tn = tile
+    for ex in range(2):
+        for ls in (0, (T - 1) // 64):
+            part = slice(ex * T + 64 * ls, min(ex * T + 64 * ls + 64, (ex + 1) * T))
+            ref = (G[part].T @ A[part])[384 * tm:384 * tm + 384, 256 * tn:256 * tn + 256]
+            got = padded_slice(G, A, T, tm, tn, ex, ls)
+            np.testing.assert_allclose(got[:ref.shape[0], :ref.shape[1]], ref, atol=1e-9)
 
 
 # ------------------------------------------- float32 Gram form (gram64_kernel)
@@ -299,6 +372,34 @@ def test_skinny_mfma_lanes_form_the_gradient(T, d_w, r, narrow_is_a, chunk, t0, 
     np.testing.assert_allclose(got[sl], ref[sl], rtol=1e-12, atol=1e-12)
     # The wave's norm partial (every output, zeros included) is the chunk's.
     assert math.isclose(float(np.sum(acc ** 2)), float(np.sum(ref[sl] ** 2)), rel_tol=1e-12)
+
+@pytest.mark.parametrize("T,d_w,r,t0,t1", [(37, 256, 16, 0, 37), (203, 768, 8, 100, 203),
+                                           (64, 8, 4, 0, 64), (65, 136, 12, 33, 65)])
+def test_skinny_mfma_loads_stay_in_the_range(T, d_w, r, t0, t1):
+    """The clamped loads of a wave (offsets in elements from the range's first row)
+    lie inside rows [t0, t1) and are the intended ones for every row of the range;
+    no block is loaded past the last one."""
+    nr = t1 - t0
+    assert 0 <= t0 < t1 <= T
+    for chunk in range(-(-d_w // 128)):
+        for tr in range(0, nr, 32):
+            for lane in range(64):
+                g, cl = lane >> 4, lane & 15
+                col = 128 * chunk + 8 * cl
+                woff = 8 * g * d_w + (col if col < d_w else 0)
+                for kk in range(8):
+                    row = min(tr + kk, nr - 1)
+                    at = row * d_w + min(woff, min(nr - row, 25) * d_w - 8)
+                    assert 0 <= at and at + 8 <= nr * d_w
+                    if tr + 8 * g + kk < nr and col < d_w:
+                        assert at == (tr + 8 * g + kk) * d_w + col
+                left = nr - tr
+                last = min(left, 32) * (r >> 2) - 1          # 8-byte chunks of the narrow run
+                for c in (lane, 64 + lane):
+                    at = tr * r + 4 * min(c, last)
+                    assert at + 4 <= nr * r
+                    if c < left * (r >> 2):
+                        assert at == tr * r + 4 * c or c >= 32 * (r >> 2)
 
 
 # ------------------------- bf16 Gram form on 256-row tiles (ghost_tile256_kernel)
