@@ -33,16 +33,19 @@
 // v_mfma_f32_32x32x2_f32 in 3/8 of the cycles. An infinity has no such parts
 // (inf - inf is NaN, and so is inf times a zero part), and operands from 2^103
 // or sums from 2^80 leave the range when scaled, so a wave whose result is not
-// finite recomputes its block with float32 MFMAs (recompute_f32).
+// finite recomputes its block with float32 MFMAs (recompute_f32: about five times
+// the time of a sum whose every wave does; a NaN clip factor, after which all
+// entries are NaN, is told apart first).
 // What bounds it: the matrix cores and, next to them, the conversion on the
 // VALU (5.5 instructions an element), so the loads' addresses cost one
 // instruction each (a scalar base and a fixed 32-bit lane offset).
 // The sixteen convolutions of WRN-16-4 (B = 256, T = 1024, 256 and 64; 343
 // GFLOP in all): norms of the materialised ones 1.53 -> 1.05 ms and clipped
-// sums 2.18 -> 1.44 ms against float32 MFMAs, the whole call 3.91 -> 2.46 ms
+// sums 2.18 -> 1.41 ms against float32 MFMAs, the whole call 3.91 -> 2.49 ms
 // (two accumulator sets included, which cost 10 % but bring the error against
-// float64 from 2.1e-6 to 4.6e-7; 6.7e-7 before). A launch of 137 GFLOP takes
-// 0.89 ms: with six products each 0.93 PFLOP/s at 1.5 GHz, the power limit.
+// float64 from 2.1e-6 to 4.4e-7; 6.8e-7 before; the scaling costs 1 %). A launch
+// of 137 GFLOP takes 0.85 ms: with six products each 0.97 PFLOP/s, 70 % of what a
+// large bf16 product reaches here (1.5 GHz in a loop of them: the power limit).
 // bf16, T = 1 (768 -> 768 and 768 -> 10, B = 2048): 72 -> 17 us.
 //
 // Clip weights. FLAT (float32, and bf16 with short or badly padded T): rows
@@ -610,7 +613,17 @@ __device__ __forceinline__ void any_job(const AnyArgs& args, const AnyEntry& E, 
       for (int b = 0; b < C::kNB; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) bad = fmaf(acc[a][b][v], 0.0f, bad);
-    if (__builtin_amdgcn_ballot_w64(bad != bad) != 0)
+    bool again = __builtin_amdgcn_ballot_w64(bad != bad) != 0;
+    if (again) {
+      // A NaN factor makes every entry NaN, which it is already.
+      bool nan = false;
+      for (int64_t i = k0 / T + lane; i <= (k1 - 1) / T; i += 64) {
+        const float c = NSQ ? clip_factor(args.norms_sq[i], args.C) : args.factors[i];
+        nan = nan || c != c;
+      }
+      again = __builtin_amdgcn_ballot_w64(nan) == 0;
+    }
+    if (again)
       recompute_f32<C::kMB, C::kNB>(reinterpret_cast<const float*>(Gb),
                                     reinterpret_cast<const float*>(Ab), M, N, m_base, n_base, k0, k1,
                                     T, NSQ ? nullptr : args.factors, NSQ ? args.norms_sq : nullptr,

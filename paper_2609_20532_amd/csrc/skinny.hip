@@ -234,8 +234,9 @@ __device__ __forceinline__ bf16x8_t skm_bits(uint32_t w0, uint32_t w1, uint32_t 
 // side alone took eight 2-byte loads. QUADS (r a multiple of 4): the narrow
 // block of 32 rows is one contiguous run, loaded 8 bytes a lane, passed through
 // LDS and read back transposed (ds_read_b64_tr_b16). 48 matrices of rank 8,
-// d = 768, B = 48, T = 203 (547 MB): 119 -> 115 us,
-// bound by its reads; rank 16, d = 4096, B = 16, T = 1024 (268 MB): 70 -> 57 us.
+// d = 768, B = 48, T = 203 (547 MB): 119 -> 116 us, 1.12 times the input bytes
+// fetched, 5.3 TB/s; rank 16, d = 4096, B = 16, T = 1024 (268 MB): 50 us, 5.3 TB/s, alone
+// and 56 beside a large layer, a call of the pair 75 us as before.
 template <bool QUADS>
 __global__ __launch_bounds__(kThreads, 3) void skinny_mfma_kernel(SkArgs args) {
   // QUADS: a wave's narrow block (1 KB at most) and 8 zero bytes for the

@@ -194,3 +194,22 @@ def test_norms_or_outputs_inside_a_gradient(dp, where):
     assert rel_err(torch_to_float64(grad), S) <= 2e-6
     if where != "factors":
         np.testing.assert_allclose(factors.cpu().numpy(), c, rtol=1e-6)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims", [(40, 130, 70), (300, 24, 16), (1, 200, 33), (1, 1000, 900)])
+def test_float32_sums_with_a_nan_factor(dp, dims):
+    """A NaN norm makes the example's factor NaN and with it every entry."""
+    import torch
+    B = 70
+    dev, ol = _layers(wl.F32, B, [dims], 29)
+    L = dev[0][0]
+    nsq = torch.from_numpy(oracle.per_example_norms_sq(ol).astype(np.float32)).cuda()
+    nsq[B - 2] = float("nan")
+    grad = torch.zeros(dims[2], dims[1], device="cuda")
+    factors = torch.empty(B, device="cuda")
+    ws = torch.empty(dp.dpsgd_clip_workspace_bytes([L]), dtype=torch.uint8, device="cuda")
+    dp.dpsgd_clip_accumulate(L, nsq, 1.0, grad, factors_out=factors, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(grad).all()
+    assert torch.isnan(factors[B - 2]) and torch.isfinite(factors).sum().item() == B - 1
