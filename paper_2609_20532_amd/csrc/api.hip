@@ -69,29 +69,36 @@ NormForm planned_form(const dpsgd_layer& L, NormForm f, bool park_ok) {
 }
 
 // Moves Gram-form layers to the materialised form where that is faster: alone,
-// or beside materialised layers of the call that leave CUs free and run as long
-// (a launch less). Its partials (one per tile) can be more than the Gram form's
+// or beside materialised layers of the call that leave CUs free and run about as
+// long (a launch less). Its partials (one per tile) can be more than the Gram form's
 // (one per tile pair): calls whose partials would not fit the allocation-free
 // call's scratch keep the Gram form, whichever entry point runs them.
 void materialise_faster(const dpsgd_layer* layers, int32_t n, int32_t mode, NormPlan* p) {
+  std::vector<int32_t> near;   // Gram-form layers that may move (few calls have any)
+  for (int32_t l = 0; l < n; ++l)
+    if (p->forms[l] == FORM_GHOST && may_materialise(layers[l], mode)) near.push_back(l);
+  if (near.empty()) return;
+  constexpr double kLaunchUs = 4.0;
+  const int64_t slots = 2 * (int64_t)tr_cu_count();
   std::vector<NormForm> forms = p->forms;
+  for (int32_t l : near)
+    if (prefer_materialised(layers[l])) forms[l] = FORM_MAT;
   double longest = 0.0;
-  int64_t cols = 0, tiles = 0;
-  for (int32_t l = 0; l < n; ++l) {
-    if (forms[l] == FORM_GHOST && prefer_materialised(layers[l], mode)) forms[l] = FORM_MAT;
+  int64_t tiles = 0;
+  for (int32_t l = 0; l < n && tiles <= slots; ++l) {
     if (forms[l] != FORM_MAT) continue;
     longest = std::max(longest, mat_us(layers[l]));
     tiles += layers[l].B * mat_tile_count(layers[l]);
   }
-  for (int32_t l = 0; l < n; ++l) {
+  for (int32_t l : near) {
+    if (forms[l] == FORM_MAT || tiles == 0) continue;
     const int64_t more = layers[l].B * mat_tile_count(layers[l]);
-    if (forms[l] == FORM_GHOST && may_materialise(layers[l], mode) && mat_us(layers[l]) <= longest &&
-        tiles + more <= 2 * (int64_t)tr_cu_count()) {
-      forms[l] = FORM_MAT;
-      tiles += more;
-    }
-    cols += norm_partials_per_example(layers[l], forms[l]);
+    if (tiles + more > slots || mat_us(layers[l]) > longest + kLaunchUs) continue;
+    forms[l] = FORM_MAT;
+    tiles += more;
   }
+  int64_t cols = 0;
+  for (int32_t l = 0; l < n; ++l) cols += norm_partials_per_example(layers[l], forms[l]);
   if ((size_t)layers[0].B * (size_t)cols * sizeof(float) <= DPSGD_NOALLOC_SCRATCH_BYTES)
     p->forms.swap(forms);
 }

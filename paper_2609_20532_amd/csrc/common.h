@@ -114,7 +114,7 @@ NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode);
 // whether that is less than the Gram form's.
 bool may_materialise(const dpsgd_layer& L, int32_t mode);
 double mat_us(const dpsgd_layer& L);
-bool prefer_materialised(const dpsgd_layer& L, int32_t mode);
+bool prefer_materialised(const dpsgd_layer& L);
 
 // Writes per-example partials partials[i * P + col_l + j] for the given layers
 // (all with the chosen forms), then reduces them into norms_sq. park: the

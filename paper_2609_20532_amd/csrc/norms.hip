@@ -775,14 +775,16 @@ NormForm resolve_norm_form(const dpsgd_layer& L, int32_t mode) {
 
 // Estimated times of the two forms in microseconds, without launches, fitted to
 // 240 layers (B = 8 to 2048, T = 50 to 512, widths 2 to 1152) within about 10 %.
-// Gram: columns of a tile, at one workgroup a CU, then two, then in rounds.
+// Gram: columns of a tile, at one workgroup a CU, then two, then in rounds (a last
+// round of one workgroup a CU takes half the time of a whole one).
 static double gram_us(const dpsgd_layer& L) {
   const bool bf16 = L.dtype == DPSGD_BF16;
   const int64_t bk = bf16 ? TileCfg<uint16_t>::BK : TileCfg<float>::BK, nt = ceil_div(L.T, kTile);
-  const double jobs = (double)(L.B * (nt * (nt + 1) / 2)), cus = (double)tr_cu_count();
+  const int64_t jobs = L.B * (nt * (nt + 1) / 2), cus = tr_cu_count(), rest = jobs % (2 * cus);
+  const double rounds = (double)(jobs / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? 0.5 : 1.0);
   const double cols = (double)((ceil_div(L.d_in, bk) + ceil_div(L.d_out, bk)) * bk);
   const double col_us = jobs <= cus ? (bf16 ? 0.018 : 0.066)
-                                    : (bf16 ? 0.022 : 0.13) * std::max(1.0, jobs / (2.0 * cus));
+                                    : (bf16 ? 0.022 : 0.13) * rounds;
   return cols * col_us * (any_slow(L) ? (bf16 ? 2.0 : 1.2) : 1.0);
 }
 // Materialised: 16-row groups of a tile alone, or of all tiles with two
@@ -814,9 +816,7 @@ bool may_materialise(const dpsgd_layer& L, int32_t mode) {
   if (mode != DPSGD_NORM_AUTO || L.T == 1 || gram64_ok(L) || ghost256_ok(L)) return false;
   return !gram_is_less(L, L.dtype == DPSGD_F32 ? 2.5 : 1.0, any_tiles_128(L));
 }
-bool prefer_materialised(const dpsgd_layer& L, int32_t mode) {
-  return may_materialise(L, mode) && mat_us(L) < gram_us(L);
-}
+bool prefer_materialised(const dpsgd_layer& L) { return mat_us(L) < gram_us(L); }
 
 int64_t norm_partials_per_example(const dpsgd_layer& L, NormForm form) {
   switch (form) {

@@ -140,12 +140,13 @@ def test_tiny_layers(dp, case):
 
 @pytest.mark.parametrize("dims,dtype,form", [
     # Gram and materialised, us: 757 and 1270, 141 and 253, 11 and 21; 283 and 119,
-    # 74 and 23, 19 and 25; 29 and 24.
+    # 74 and 23, 766 and 657 (a short second round of Gram tiles); 19 and 25, 29 and 24.
     ((512, 256, 768, 1152), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_GHOST),
     ((512, 128, 576, 512), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_GHOST),
     ((64, 256, 12, 32), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_GHOST),
     ((8, 512, 768, 3072), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_MATERIALIZE),
     ((64, 100, 768, 256), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_MATERIALIZE),
+    ((16, 1000, 1536, 2304), dpsgd.DPSGD_F32, dpsgd.DPSGD_NORM_MATERIALIZE),
     ((2048, 65, 16, 48), dpsgd.DPSGD_BF16, dpsgd.DPSGD_NORM_GHOST),
     ((2048, 65, 144, 12), dpsgd.DPSGD_BF16, dpsgd.DPSGD_NORM_MATERIALIZE),
 ])
